@@ -107,7 +107,7 @@ Layout layout_of(const sem_mesh_desc *d) {
   o.part_ax = take((size_t)b.E() * sizeof(double));  // per-element p.Ap
   o.part_rr = take((size_t)semk::stream_partials(b) * sizeof(double));
   o.part_rz = take((size_t)semk::stream_partials(b) * sizeof(double));
-  o.state = take(sizeof(CgState));
+  o.state = take(semk::kCgStates * sizeof(CgState));
   o.Dlo = o.Glo = o.minv32 = o.e = o.rin = o.pin = o.win = o.state_in = 0;
   if (d->lowprec != SEM_F64) {
     const size_t gbytes = d->lowprec == SEM_BF16 ? 2 : 4;
@@ -118,7 +118,7 @@ Layout layout_of(const sem_mesh_desc *d) {
     o.rin = take(L * sizeof(float));
     o.pin = take(L * sizeof(float));
     o.win = take(L * sizeof(float));
-    o.state_in = take(sizeof(CgState));
+    o.state_in = take(semk::kCgStates * sizeof(CgState));
   }
   o.total = at;
   return o;
@@ -230,34 +230,50 @@ struct sem_ctx {
 
 namespace {
 
-// One Jacobi-PCG iteration: the operator kernel (its prologue finishes the
-// previous iteration's x += alpha p and forms the new p; its epilogue leaves
-// the partials of <p, A p>), a one-group alpha step, the update kernel (which
-// pulls the assembled, masked A p from the element-local result) and a
-// one-group step for beta, the residual and the done flag.
-int enqueue_cg_iteration(sem_ctx *c, double *x, hipStream_t s) {
+// `iters` Jacobi-PCG iterations: each the operator kernel (its prologue
+// finishes the previous iteration's x += alpha p and forms the new p; its
+// epilogue leaves the partials of <p, A p>), the alpha step, the update kernel
+// (which pulls the assembled, masked A p from the element-local result) and
+// the step for beta, the residual and the done flag.  On large meshes the two
+// steps are one-group launches; on the others (cg_folded) the kernels that use
+// their results take them, and one last step ends the run.
+int enqueue_cg_iterations(sem_ctx *c, double *x, int iters, hipStream_t s) {
   const Box &b = c->box;
-  SEM_HIP(semk::launch_ax_f64(b, c->op_impl[0], c->D, c->G, c->p, c->w, c->r, c->cg_minv, x, c->st, c->part_ax, s));
-  SEM_HIP(semk::launch_cg_alpha(c->st, c->part_ax, c->n_ax_blocks, s));
-  SEM_HIP(semk::launch_cg_update(b, c->upd_var[0], c->r, c->w, c->cg_minv, c->st, c->part_rr, c->part_rz, s));
-  SEM_HIP(semk::launch_cg_beta(c->st, c->part_rr, c->part_rz, c->n_upd_blocks, s));
+  const bool folded = semk::cg_folded(b, c->upd_var[0], c->n_ax_blocks, c->n_upd_blocks);
+  semk::CgFold f;
+  if (folded) f = semk::CgFold{c->part_rr, c->part_rz, (int)c->n_upd_blocks, c->part_ax, (int)c->n_ax_blocks};
+  for (int it = 0; it < iters; ++it) {
+    SEM_HIP(semk::launch_ax_f64(b, c->op_impl[0], c->D, c->G, c->p, c->w, c->r, c->cg_minv, x, c->st, c->part_ax, s,
+                                false, f));
+    if (!folded) SEM_HIP(semk::launch_cg_alpha(c->st, c->part_ax, c->n_ax_blocks, s));
+    SEM_HIP(semk::launch_cg_update(b, c->upd_var[0], c->r, c->w, c->cg_minv, c->st, c->part_rr, c->part_rz, s, f));
+    if (!folded) SEM_HIP(semk::launch_cg_beta(c->st, c->part_rr, c->part_rz, c->n_upd_blocks, s));
+  }
+  if (folded) SEM_HIP(semk::launch_cg_beta_pending(c->st, c->part_rr, c->part_rz, c->n_upd_blocks, s));
   return SEM_OK;
 }
 
-// One iteration of the inner (low-precision) Jacobi-PCG: the same four steps
+// `iters` iterations of the inner (low-precision) Jacobi-PCG: the same steps
 // on FP32 vectors with the rounded operator; the inner correction e plays x.
-int enqueue_inner_iteration(sem_ctx *c, double *, hipStream_t s) {
+int enqueue_inner_iterations(sem_ctx *c, double *, int iters, hipStream_t s) {
   const Box &b = c->box;
-  SEM_HIP(semk::launch_ax_lowp(b, c->desc.lowprec, c->op_impl[1], c->Dlo, c->Glo,
-                               c->pin, c->win, c->rin, c->minv32, c->e, c->st_in, c->part_ax, s));
-  SEM_HIP(semk::launch_cg_alpha(c->st_in, c->part_ax, c->n_ax_blocks, s));
-  SEM_HIP(semk::launch_cg_update_f32(b, c->upd_var[1], c->rin, c->win, c->minv32, c->st_in, c->part_rr,
-                                     c->part_rz, s));
-  SEM_HIP(semk::launch_cg_beta(c->st_in, c->part_rr, c->part_rz, c->n_upd_blocks_in, s));
+  const bool folded = semk::cg_folded(b, c->upd_var[1], c->n_ax_blocks, c->n_upd_blocks_in);
+  semk::CgFold f;
+  if (folded)
+    f = semk::CgFold{c->part_rr, c->part_rz, (int)c->n_upd_blocks_in, c->part_ax, (int)c->n_ax_blocks};
+  for (int it = 0; it < iters; ++it) {
+    SEM_HIP(semk::launch_ax_lowp(b, c->desc.lowprec, c->op_impl[1], c->Dlo, c->Glo, c->pin, c->win, c->rin,
+                                 c->minv32, c->e, c->st_in, c->part_ax, s, false, f));
+    if (!folded) SEM_HIP(semk::launch_cg_alpha(c->st_in, c->part_ax, c->n_ax_blocks, s));
+    SEM_HIP(semk::launch_cg_update_f32(b, c->upd_var[1], c->rin, c->win, c->minv32, c->st_in, c->part_rr,
+                                       c->part_rz, s, f));
+    if (!folded) SEM_HIP(semk::launch_cg_beta(c->st_in, c->part_rr, c->part_rz, c->n_upd_blocks_in, s));
+  }
+  if (folded) SEM_HIP(semk::launch_cg_beta_pending(c->st_in, c->part_rr, c->part_rz, c->n_upd_blocks_in, s));
   return SEM_OK;
 }
 
-typedef int (*enqueue_fn)(sem_ctx *, double *, hipStream_t);
+typedef int (*enqueue_fn)(sem_ctx *, double *, int, hipStream_t);
 
 void drop_graph(sem_ctx *c, int slot) {
   if (c->graph[slot]) (void)hipGraphExecDestroy(c->graph[slot]);
@@ -281,8 +297,7 @@ int capture_graph(sem_ctx *c, int slot, enqueue_fn fn, double *x, int iters, hip
     (void)hipGetLastError();
     return 1;
   }
-  int rc = SEM_OK;
-  for (int it = 0; it < iters && rc == SEM_OK; ++it) rc = fn(c, x, s);
+  const int rc = fn(c, x, iters, s);
   hipGraph_t g = nullptr;
   hipError_t e = hipStreamEndCapture(s, &g);
   if (rc != SEM_OK) {
@@ -314,10 +329,8 @@ int run_until_done(sem_ctx *c, int slot, enqueue_fn fn, double *x, CgState *st, 
     if (use_graph) {
       SEM_HIP(hipGraphLaunch(c->graph[slot], s));
     } else {
-      for (int it = 0; it < every; ++it) {
-        rc = fn(c, x, s);
-        if (rc != SEM_OK) return rc;
-      }
+      rc = fn(c, x, every, s);
+      if (rc != SEM_OK) return rc;
     }
     launched += every;
     SEM_HIP(hipMemcpyAsync(host, st, sizeof(CgState), hipMemcpyDeviceToHost, s));
@@ -519,7 +532,7 @@ int sem_cg(sem_ctx *ctx, const double *b, double *x, const sem_cg_opts *opts, se
   int status = SEM_OK;
   if (!opts->mixed) {
     if (every > max_iter) every = max_iter;
-    int rc = run_until_done(ctx, 0, enqueue_cg_iteration, x, ctx->st, &h, every, max_iter, s);
+    int rc = run_until_done(ctx, 0, enqueue_cg_iterations, x, ctx->st, &h, every, max_iter, s);
     if (rc != SEM_OK) return rc;
     SEM_HIP(semk::launch_cg_finish(ctx->box, x, ctx->p, ctx->st, s));
     SEM_HIP(hipStreamSynchronize(s));
@@ -542,7 +555,7 @@ int sem_cg(sem_ctx *ctx, const double *b, double *x, const sem_cg_opts *opts, se
       SEM_HIP(semk::launch_inner_start(bx, ctx->r, ctx->st, ctx->st_in, eta * eta, inner_max, ctx->rin,
                                        ctx->e, ctx->pin, ctx->minv32, ctx->part_rz, ctx->part_rr, s));
       CgState &hi = ctx->host_inner;
-      int rc = run_until_done(ctx, 1, enqueue_inner_iteration, nullptr, ctx->st_in, &hi, every,
+      int rc = run_until_done(ctx, 1, enqueue_inner_iterations, nullptr, ctx->st_in, &hi, every,
                               inner_max, s);
       if (rc != SEM_OK) return rc;
       inner_total += hi.iter;

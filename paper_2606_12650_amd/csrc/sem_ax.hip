@@ -30,14 +30,19 @@ __global__ void __launch_bounds__(256)
 
 template <int N1, class P>
 hipError_t ax_dispatch(const Box &b, const void *D, const void *G, void *u, void *w, const void *r,
-                       const void *minv, void *x, CgState *cg, double *part, hipStream_t s) {
+                       const void *minv, void *x, CgState *cg, double *part, hipStream_t s,
+                       const CgFold &fold) {
   using C = OpCfg<N1>;
   using TV = typename P::TV;
   using TG = typename P::TG;
   using TC = typename P::TC;
   const int64_t blocks = (b.E() + C::EPB - 1) / C::EPB;
   if (blocks == 0) return hipSuccess;
-  if (cg)
+  if (cg && fold.n_upd > 0)
+    hipLaunchKernelGGL((ax_fold_kernel<N1, P>), dim3((unsigned)blocks), dim3(C::THREADS), 0, s, b.E(),
+                       (const TC *)D, (const TG *)G, (TV *)u, (TV *)w, (const TV *)r, (const TV *)minv,
+                       (TV *)x, cg, part, fold.part_rr, fold.part_rz, fold.n_upd);
+  else if (cg)
     hipLaunchKernelGGL((ax_kernel<N1, P, true>), dim3((unsigned)blocks), dim3(C::THREADS), 0, s,
                        b.E(), (const TC *)D, (const TG *)G, (TV *)u, (TV *)w, (const TV *)r,
                        (const TV *)minv, (TV *)x, cg, part);
@@ -51,14 +56,18 @@ hipError_t ax_dispatch(const Box &b, const void *D, const void *G, void *u, void
 template <int N1, class P>
 hipError_t mfma_dispatch(const Box &b, const void *D, const void *G, void *u, void *w, const void *r,
                          const void *minv, void *x, CgState *cg, double *part, hipStream_t s,
-                         bool stream_w) {
+                         bool stream_w, const CgFold &fold) {
   using C = MfmaCfg<N1>;
   using TV = typename P::TV;
   using TG = typename P::TG;
   using TC = typename P::TC;
   const int64_t blocks = (b.E() + C::EPB - 1) / C::EPB;
   if (blocks == 0) return hipSuccess;
-  if (cg)
+  if (cg && fold.n_upd > 0)
+    hipLaunchKernelGGL((ax_mfma_fold_kernel<N1, P>), dim3((unsigned)blocks), dim3(C::THREADS), 0, s, b.E(),
+                       (const TC *)D, (const TG *)G, (TV *)u, (TV *)w, (const TV *)r, (const TV *)minv,
+                       (TV *)x, cg, part, fold.part_rr, fold.part_rz, fold.n_upd);
+  else if (cg)
     hipLaunchKernelGGL((ax_mfma_kernel<N1, P, true>), dim3((unsigned)blocks), dim3(C::THREADS), 0, s,
                        b.E(), (const TC *)D, (const TG *)G, (TV *)u, (TV *)w, (const TV *)r,
                        (const TV *)minv, (TV *)x, cg, part);
@@ -110,13 +119,13 @@ int64_t ax_num_blocks(const Box &b) {
 template <class P>
 hipError_t ax_launch(const Box &b, int cls, int impl, const void *D, const void *G, void *u, void *w,
                      const void *r, const void *minv, void *x, CgState *cg, double *part,
-                     hipStream_t s, bool stream_w) {
+                     hipStream_t s, bool stream_w, const CgFold &fold) {
   const bool mfma = impl == kImplMfma || (impl == kImplDefault && op_uses_mfma(cls, b.N));
   switch (b.N) {
 #define CASE(n)                                                                      \
   case n:                                                                            \
-    return mfma ? mfma_dispatch<n + 1, P>(b, D, G, u, w, r, minv, x, cg, part, s, stream_w) \
-                : ax_dispatch<n + 1, P>(b, D, G, u, w, r, minv, x, cg, part, s);
+    return mfma ? mfma_dispatch<n + 1, P>(b, D, G, u, w, r, minv, x, cg, part, s, stream_w, fold) \
+                : ax_dispatch<n + 1, P>(b, D, G, u, w, r, minv, x, cg, part, s, fold);
     SEM_FOR_EACH_ORDER(CASE)
 #undef CASE
     default:
@@ -126,19 +135,19 @@ hipError_t ax_launch(const Box &b, int cls, int impl, const void *D, const void 
 
 hipError_t launch_ax_f64(const Box &b, int impl, const double *D, const double *G, double *u,
                          double *w, const double *r, const double *minv, double *x, CgState *cg,
-                         double *part, hipStream_t s, bool stream_w) {
+                         double *part, hipStream_t s, bool stream_w, const CgFold &fold) {
   if (rtc_order(b.N))  // run-time kernels: the matrix-core tile only
     return impl == kImplValu ? hipErrorInvalidValue : rtc_ax_f64(b, D, G, u, w, r, minv, x, cg, part, s);
-  return ax_launch<PrecF64>(b, 0, impl, D, G, u, w, r, minv, x, cg, part, s, stream_w);
+  return ax_launch<PrecF64>(b, 0, impl, D, G, u, w, r, minv, x, cg, part, s, stream_w, fold);
 }
 
 hipError_t launch_ax_lowp(const Box &b, int prec, int impl, const float *D, const void *G, float *u,
                           float *w, const float *r, const float *minv, float *x, CgState *cg,
-                          double *part, hipStream_t s, bool stream_w) {
+                          double *part, hipStream_t s, bool stream_w, const CgFold &fold) {
   if (prec == SEM_F32)
-    return ax_launch<PrecF32>(b, 1, impl, D, G, u, w, r, minv, x, cg, part, s, stream_w);
+    return ax_launch<PrecF32>(b, 1, impl, D, G, u, w, r, minv, x, cg, part, s, stream_w, fold);
   if (prec == SEM_BF16)
-    return ax_launch<PrecBF16>(b, 2, impl, D, G, u, w, r, minv, x, cg, part, s, stream_w);
+    return ax_launch<PrecBF16>(b, 2, impl, D, G, u, w, r, minv, x, cg, part, s, stream_w, fold);
   return hipErrorInvalidValue;
 }
 

@@ -217,14 +217,14 @@ __device__ __forceinline__ void mfma_store(typename P::TC *out, const typename M
 // nodes in index order (thread t: nodes t, t + 64 NT, ...), so every load and
 // store is a run of 64 consecutive values.  The t-direction results pass
 // through LDS to meet that layout.
-template <int N1, int EPB, class P, bool CG, bool OPQ = false, bool SW = false>
+template <int N1, int EPB, class P, bool CG, bool OPQ = false, bool SW = false, class SC = GivenScalars>
 __device__ __forceinline__ void ax_tile_mfma(int64_t E, int64_t e0, const typename P::TC *__restrict__ Dg,
                                              const typename P::TG *__restrict__ G, typename P::TV *u,
                                              typename P::TV *__restrict__ w,
                                              const typename P::TV *__restrict__ r,
                                              const typename P::TV *__restrict__ minv,
-                                             typename P::TV *__restrict__ x, double alpha_d,
-                                             double beta_d, double *__restrict__ part_el,
+                                             typename P::TV *__restrict__ x, SC scalars,
+                                             double *__restrict__ part_el,
                                              typename P::TC *sD, typename P::TC *s1,
                                              typename P::TC *s2, typename P::TC *s3,
                                              double *sred) {
@@ -294,6 +294,9 @@ __device__ __forceinline__ void ax_tile_mfma(int64_t E, int64_t e0, const typena
     }
   };
   if constexpr (!LATE_G) load_gk();
+  double alpha_d = 0.0, beta_d = 0.0;
+  if (CG)  // uniform: a stopped solve skips all work
+    if (!scalars(&alpha_d, &beta_d)) return;
   TC uk[PPT];
 #pragma unroll
   for (int m = 0; m < PPT; ++m) {

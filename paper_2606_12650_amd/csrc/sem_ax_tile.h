@@ -10,6 +10,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include "sem_cg_dev.h"
 #include "sem_device.h"
 #include "sem_types.h"
 
@@ -37,13 +38,13 @@ struct AxTile {
 //   per-element sums of p.(A_L p) go to part_el[e] (summed in a fixed tree).
 // sD: N1*N1, s1/s2 (and s3 when AxTile<N1>::kTiles == 3): EPB *
 // AxTile<N1>::TILE values of TC each, sred: blockDim doubles, all in LDS.
-template <int N1, int EPB, class P, bool CG, bool OPQ = false>
+template <int N1, int EPB, class P, bool CG, bool OPQ = false, class SC = GivenScalars>
 __device__ __forceinline__ void ax_tile_col(int64_t E, int64_t e0, const typename P::TC *__restrict__ Dg,
                                         const typename P::TG *__restrict__ G, typename P::TV *u,
                                         typename P::TV *__restrict__ w,
                                         const typename P::TV *__restrict__ r,
                                         const typename P::TV *__restrict__ minv,
-                                        typename P::TV *__restrict__ x, double alpha_d, double beta_d,
+                                        typename P::TV *__restrict__ x, SC scalars,
                                         double *__restrict__ part_el, typename P::TC *sD,
                                         typename P::TC *s1, typename P::TC *s2,
                                         typename P::TC *s3, double *sred) {
@@ -69,21 +70,17 @@ __device__ __forceinline__ void ax_tile_col(int64_t E, int64_t e0, const typenam
   const typename P::TG *Ge = G + (active ? e : 0) * 6 * NP + ij;
   TC uk[N1];  // the operand (p in CG), in the contraction type
   TC g[6][kPrefetchG ? N1 : 1];
+  TV pv[N1], xv[CG ? N1 : 1], mv[CG ? N1 : 1], rv[CG ? N1 : 1];
   if (active) {
-    if (CG) {
-      const TV beta = (TV)beta_d, alpha = (TV)alpha_d;
 #pragma unroll
-      for (int k = 0; k < N1; ++k) {
-        const int64_t idx = base + k * PL;
-        const TV pold = ld_once(u + idx);
-        st_once(x + idx, ld_once(x + idx) + alpha * pold);
-        const TV v = minv_at(minv, r, idx) * ld_once(r + idx) + beta * pold;
-        uk[k] = (TC)v;
-        st_once(u + idx, v);
+    for (int k = 0; k < N1; ++k) {
+      const int64_t idx = base + k * PL;
+      pv[k] = ld_once(u + idx);
+      if constexpr (CG) {
+        xv[k] = ld_once(x + idx);
+        mv[k] = minv_at(minv, r, idx);
+        rv[k] = ld_once(r + idx);
       }
-    } else {
-#pragma unroll
-      for (int k = 0; k < N1; ++k) uk[k] = (TC)ld_once(u + base + k * PL);
     }
     if constexpr (kPrefetchG) {
 #pragma unroll
@@ -94,13 +91,31 @@ __device__ __forceinline__ void ax_tile_col(int64_t E, int64_t e0, const typenam
   } else {
 #pragma unroll
     for (int k = 0; k < N1; ++k) {
-      uk[k] = (TC)0;
+      pv[k] = (TV)0;
+      if constexpr (CG) xv[k] = mv[k] = rv[k] = (TV)0;
       if constexpr (kPrefetchG) {
 #pragma unroll
         for (int q = 0; q < 6; ++q) g[q][k] = (TC)0;
       }
     }
   }
+  if constexpr (CG) {
+    double alpha_d, beta_d;
+    if (!scalars(&alpha_d, &beta_d)) return;  // uniform: a stopped solve skips all work
+    const TV beta = (TV)beta_d, alpha = (TV)alpha_d;
+#pragma unroll
+    for (int k = 0; k < N1; ++k) {
+      const TV v = mv[k] * rv[k] + beta * pv[k];
+      if (active) {
+        const int64_t idx = base + k * PL;
+        st_once(x + idx, xv[k] + alpha * pv[k]);
+        st_once(u + idx, v);
+      }
+      pv[k] = v;
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < N1; ++k) uk[k] = (TC)pv[k];
 
   TC uc[N1];  // contraction input (rounded to bfloat16 in that mode)
 #pragma unroll
@@ -213,14 +228,14 @@ __device__ __forceinline__ void ax_tile_col(int64_t E, int64_t e0, const typenam
 // parts to s2 and s3, the t part to s1 once the operand is no longer read),
 // and the transposed contractions read it back.  LDS as ax_tile with three
 // tiles; sred: blockDim doubles.
-template <int N1, int EPB, class P, bool CG, bool OPQ = false>
+template <int N1, int EPB, class P, bool CG, bool OPQ = false, class SC = GivenScalars>
 __device__ __forceinline__ void ax_tile_split(int64_t E, int64_t e0, const typename P::TC *__restrict__ Dg,
                                               const typename P::TG *__restrict__ G, typename P::TV *u,
                                               typename P::TV *__restrict__ w,
                                               const typename P::TV *__restrict__ r,
                                               const typename P::TV *__restrict__ minv,
-                                              typename P::TV *__restrict__ x, double alpha_d,
-                                              double beta_d, double *__restrict__ part_el,
+                                              typename P::TV *__restrict__ x, SC scalars,
+                                              double *__restrict__ part_el,
                                               typename P::TC *sD, typename P::TC *s1,
                                               typename P::TC *s2, typename P::TC *s3, double *sred) {
   using T = AxTile<N1>;
@@ -266,6 +281,9 @@ __device__ __forceinline__ void ax_tile_split(int64_t E, int64_t e0, const typen
       rv[kk] = ld_once(r + idx[kk]);
     }
   }
+  double alpha_d = 0.0, beta_d = 0.0;
+  if (CG)  // uniform: a stopped solve skips all work
+    if (!scalars(&alpha_d, &beta_d)) return;
 #pragma unroll
   for (int kk = 0; kk < KH; ++kk) {
     const int kc = min(k0 + kk, N1 - 1);
@@ -363,22 +381,20 @@ __device__ __forceinline__ void ax_tile_split(int64_t E, int64_t e0, const typen
 // element (the first EPB * TPE threads of the work-group; any others only
 // join the barriers).  Same contract for both layouts.  OPQ: the caller loops
 // over tiles in a persistent kernel (see opaque_tid).
-template <int N1, int EPB, class P, bool CG, bool OPQ = false>
+template <int N1, int EPB, class P, bool CG, bool OPQ = false, class SC = GivenScalars>
 __device__ __forceinline__ void ax_tile(int64_t E, int64_t e0, const typename P::TC *__restrict__ Dg,
                                         const typename P::TG *__restrict__ G, typename P::TV *u,
                                         typename P::TV *__restrict__ w,
                                         const typename P::TV *__restrict__ r,
                                         const typename P::TV *__restrict__ minv,
-                                        typename P::TV *__restrict__ x, double alpha_d, double beta_d,
+                                        typename P::TV *__restrict__ x, SC scalars,
                                         double *__restrict__ part_el, typename P::TC *sD,
                                         typename P::TC *s1, typename P::TC *s2,
                                         typename P::TC *s3, double *sred) {
   if constexpr (AxTile<N1>::kSplit)
-    ax_tile_split<N1, EPB, P, CG, OPQ>(E, e0, Dg, G, u, w, r, minv, x, alpha_d, beta_d, part_el, sD, s1,
-                                  s2, s3, sred);
+    ax_tile_split<N1, EPB, P, CG, OPQ>(E, e0, Dg, G, u, w, r, minv, x, scalars, part_el, sD, s1, s2, s3, sred);
   else
-    ax_tile_col<N1, EPB, P, CG, OPQ>(E, e0, Dg, G, u, w, r, minv, x, alpha_d, beta_d, part_el, sD, s1,
-                                s2, s3, sred);
+    ax_tile_col<N1, EPB, P, CG, OPQ>(E, e0, Dg, G, u, w, r, minv, x, scalars, part_el, sD, s1, s2, s3, sred);
 }
 
 }  // namespace semk

@@ -235,15 +235,13 @@ __device__ __forceinline__ void batch_tile(int64_t E, int64_t e0, const typename
                                            const typename P::TG *G, typename P::TV *u,
                                            typename P::TV *w, const typename P::TV *r,
                                            const typename P::TV *minv, typename P::TV *x,
-                                           double alpha, double beta, double *part,
+                                           const GivenScalars &sc, double *part,
                                            typename P::TC *sD, typename P::TC *s1,
                                            typename P::TC *s2, typename P::TC *s3, double *sred) {
   if constexpr (MFMA)
-    ax_tile_mfma<N1, EPB, P, CG, true>(E, e0, D, G, u, w, r, minv, x, alpha, beta, part, sD, s1, s2, s3,
-                                 sred);
+    ax_tile_mfma<N1, EPB, P, CG, true>(E, e0, D, G, u, w, r, minv, x, sc, part, sD, s1, s2, s3, sred);
   else
-    ax_tile<N1, EPB, P, CG, true>(E, e0, D, G, u, w, r, minv, x, alpha, beta, part, sD, s1, s2, s3,
-                                  sred);
+    ax_tile<N1, EPB, P, CG, true>(E, e0, D, G, u, w, r, minv, x, sc, part, sD, s1, s2, s3, sred);
 }
 
 template <int N1, int EPB, int CLS, bool MFMA>
@@ -282,15 +280,17 @@ __global__ void __launch_bounds__((OpCfg<N1, EPB, MFMA>::THREADS))
     const int64_t e0 = (int64_t)(w - first) * EPB;
     if constexpr (CLS == 0) {
       batch_tile<N1, EPB, PrecF64, true, MFMA>(S.E, e0, S.D, S.G, S.p, S.w, S.r, S.minv, S.x,
-                                               S.st->alpha, S.st->beta, S.part_el, sD, s1, s2, s3,
-                                               sred);
+                                               GivenScalars{S.st->alpha, S.st->beta}, S.part_el, sD, s1,
+                                               s2, s3, sred);
     } else if constexpr (CLS == 3) {  // true-residual operator of a mixed solve's outer step
       batch_tile<N1, EPB, PrecF64, false, MFMA>(S.E, e0, S.D, S.G, S.x, S.w, nullptr, nullptr,
-                                                nullptr, 0.0, 0.0, S.part_el, sD, s1, s2, s3, sred);
+                                                nullptr, GivenScalars{0.0, 0.0}, S.part_el, sD, s1, s2, s3,
+                                                sred);
     } else {
       batch_tile<N1, EPB, P, true, MFMA>(S.E, e0, S.Dlo, (const typename P::TG *)S.Glo, S.pin,
-                                         S.win, S.rin, S.minv32, S.e, S.st_in->alpha,
-                                         S.st_in->beta, S.part_el, sD, s1, s2, s3, sred);
+                                         S.win, S.rin, S.minv32, S.e,
+                                         GivenScalars{S.st_in->alpha, S.st_in->beta}, S.part_el, sD, s1, s2,
+                                         s3, sred);
     }
   }
 }
@@ -428,7 +428,7 @@ __global__ void __launch_bounds__((BatchUpd<N1, MIXED>::BLOCK))
     }
     const int tile = w - first;
     if (tile >= ut) continue;
-    const TileSums t = cg_update_tile<N1, TV>(box, tile, r, wv, minv, alpha, sA, sred,
+    const TileSums t = cg_update_tile<N1, TV>(box, tile, r, wv, minv, GivenScalars{alpha, 0.0}, sA, sred,
                                               (int)threadIdx.x);
     if (threadIdx.x == 0) {
       prr[tile] = t.a;

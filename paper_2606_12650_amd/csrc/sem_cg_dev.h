@@ -17,7 +17,7 @@
 
 namespace semk {
 
-constexpr int kFinThreads = 1024;
+constexpr int kFinThreads = kFinGroup;
 
 struct TileSums {
   double a, b;
@@ -227,14 +227,14 @@ struct LinItems {
   }
 };
 
-template <int N1, typename TV>
+template <int N1, typename TV, class SC>
 __device__ inline TileSums cg_update_tile_linear(const Box &b, int64_t tile, TV *__restrict__ r,
                                                  const TV *__restrict__ w,
-                                                 const TV *__restrict__ minv, double alpha,
+                                                 const TV *__restrict__ minv, SC scalars,
                                                  double *sred, int tid) {
   static_assert(kVecItems % kLinGroup == 0, "linear update groups must tile the items");
   const LinItems<N1> P(b, tile, tid);
-  const TV alpha_v = (TV)alpha;
+  TV alpha_v = (TV)0;
   double rr = 0.0, rz = 0.0;
   // the new r of every item is stored at the end: a store issued between
   // two groups held the next group's loads back until it had completed
@@ -255,6 +255,11 @@ __device__ inline TileSums cg_update_tile_linear(const Box &b, int64_t tile, TV 
 #pragma unroll
       for (int q = 0; q < 8; ++q)
         v[u][q] = LinItems<N1>::has_copy(t.sh, q) ? w[t.lo + P.off(q)] : (TV)0;
+    }
+    if (g == 0) {
+      double alpha, unused;
+      if (!scalars(&alpha, &unused)) return TileSums{0.0, 0.0};
+      alpha_v = (TV)alpha;
     }
 #pragma unroll
     for (int u = 0; u < kLinGroup; ++u) {
@@ -384,14 +389,14 @@ __device__ inline void column_copy_sums(const ColumnPos<N1, TV, V> &p, const TV 
   for (int kk = 0; kk < KN; ++kk) S[kk] = p.hx ? A[kk] + X[kk] : A[kk];
 }
 
-template <int N1, typename TV, int V = 0>
+template <int N1, typename TV, int V = 0, class SC>
 __device__ inline TileSums cg_update_tile(const Box &b, int64_t tile, TV *__restrict__ r,
                                           const TV *__restrict__ w, const TV *__restrict__ minv,
-                                          double alpha, double *sA, double *sred,
+                                          SC scalars, double *sA, double *sred,
                                           int tid) {
   using U = UpdTile<N1, TV, V>;
   if constexpr (U::LINEAR)
-    return cg_update_tile_linear<N1, TV>(b, tile, r, w, minv, alpha, sred, tid);
+    return cg_update_tile_linear<N1, TV>(b, tile, r, w, minv, scalars, sred, tid);
   constexpr int N = U::N, COLS = U::COLS, KN = U::KN;
   const ColumnPos<N1, TV, V> p(b, tile, tid);
   // the copies of w are summed, and r updated, in the vector type (FP64, or
@@ -405,6 +410,8 @@ __device__ inline TileSums cg_update_tile(const Box &b, int64_t tile, TV *__rest
   }
   TV S[KN];
   column_copy_sums<N1, TV, V, TV>(p, w, sA, S);
+  double alpha, unused;
+  if (!scalars(&alpha, &unused)) return TileSums{0.0, 0.0};
   const TV alpha_v = (TV)alpha;
   double rr = 0.0, rz = 0.0;
 #pragma unroll
@@ -516,6 +523,18 @@ __device__ inline void cg_init_step(CgState *st, const double *__restrict__ part
   }
 }
 
+// The done flag after <p, A p>_c: kBreakdown unless it is positive and finite.
+__device__ __forceinline__ int cg_alpha_done(double pap) {
+  return (!(pap > 0.0) || !isfinite(pap)) ? kBreakdown : kRunning;
+}
+
+// The done flag after an update that left ||r||_c^2 = rrt, as the it-th.
+__device__ __forceinline__ int cg_beta_done(double rrt, double beta, double tol2, int it, int max_iter) {
+  if (!isfinite(rrt) || !isfinite(beta)) return kBreakdown;
+  if (tol2 >= 0.0 && rrt <= tol2) return kConverged;
+  return it >= max_iter ? kMaxIter : kRunning;
+}
+
 // alpha = rho / <p, A p>_c (or breakdown) from the per-element partials.
 __device__ inline void cg_alpha_step(CgState *st, const double *__restrict__ part, int64_t n,
                                      double *sred) {
@@ -525,12 +544,11 @@ __device__ inline void cg_alpha_step(CgState *st, const double *__restrict__ par
   const double pap = sum_partials<kFinThreads>(part, n, sred);
   if (threadIdx.x == 0 && done == kRunning) {
     st->pap = pap;
-    if (!(pap > 0.0) || !isfinite(pap)) {
-      st->done = kBreakdown;
+    st->done = cg_alpha_done(pap);
+    if (st->done != kRunning)
       st->done_stage = 1;
-    } else {
+    else
       st->alpha = rho / pap;
-    }
   }
 }
 
@@ -550,16 +568,112 @@ __device__ inline void cg_beta_step(CgState *st, const double *__restrict__ part
     const double beta = rzt / rho;
     st->beta = beta;
     st->rho = rzt;
-    if (!isfinite(rrt) || !isfinite(beta)) {
-      st->done = kBreakdown;
-    } else if (tol2 >= 0.0 && rrt <= tol2) {
-      st->done = kConverged;
-    } else if (it >= max_iter) {
-      st->done = kMaxIter;
-    }
+    st->done = cg_beta_done(rrt, beta, tol2, it, max_iter);
     st->done_stage = 2;
+    st->pending = 0;
   }
 }
+
+// Where a CG operator or update launch has its scalars from: given (read from
+// the state by the caller), or, in folded iterations, worked out by every
+// work-group for itself from the partials of the launch before.  A tile calls
+// it once all its loads are in flight and takes no further part if it returns
+// false (the solve has stopped; uniform over the launch).
+struct GivenScalars {
+  double alpha, beta;
+  __device__ __forceinline__ bool operator()(double *a, double *b) const {
+    *a = alpha;
+    *b = beta;
+    return true;
+  }
+};
+
+// The operator's scalars in a folded iteration: alpha of the iteration before
+// (for x += alpha p) and beta, from the state and the partials of the last
+// update, whose beta step is taken here.  Work-group 0 writes the resulting
+// state to the second place, for the update launch.  W: full waves of the
+// work-group; sred: 32 doubles.
+template <int W>
+struct FoldBeta {
+  CgState *st;
+  double *sred;
+  PartialSums<W, 2> ps;
+  double rho, pap, rnorm2, bnorm2, rtol2, tol2, alpha0, beta0;
+  int done, iter, max_iter, stage, pending;
+  __device__ __forceinline__ FoldBeta(CgState *__restrict__ s, const double *__restrict__ part_rr,
+                                      const double *__restrict__ part_rz, int n, double *sr)
+      : st(s), sred(sr) {
+    ps.load(part_rr, part_rz, n);
+    done = s->done; iter = s->iter; max_iter = s->max_iter; stage = s->done_stage; pending = s->pending;
+    rho = s->rho; pap = s->pap; rnorm2 = s->rnorm2; bnorm2 = s->bnorm2; rtol2 = s->rtol2; tol2 = s->tol2;
+    alpha0 = s->alpha; beta0 = s->beta;
+  }
+  __device__ __forceinline__ bool operator()(double *a, double *b) {
+    double rrt, rzt;
+    ps.finish(sred, &rrt, &rzt);
+    if (done == kRunning && pending) {
+      ++iter;
+      rnorm2 = rrt;
+      beta0 = rzt / rho;
+      rho = rzt;
+      done = cg_beta_done(rrt, beta0, tol2, iter, max_iter);
+      stage = 2;
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+      CgState *n = st + 1;
+      n->done = done; n->iter = iter; n->max_iter = max_iter; n->done_stage = stage; n->pending = 0;
+      n->rho = rho; n->pap = pap; n->rnorm2 = rnorm2; n->bnorm2 = bnorm2; n->rtol2 = rtol2; n->tol2 = tol2;
+      n->alpha = alpha0; n->beta = beta0;
+    }
+    *a = alpha0;
+    *b = beta0;
+    return done == kRunning;
+  }
+};
+
+// The update's alpha in a folded iteration, from the second state and the
+// partials of the operator.  Work-group 0 writes the resulting state to the
+// first place, with the beta step of this update still to be done.  sred: 16
+// doubles.
+template <int W>
+struct FoldAlpha {
+  CgState *st;
+  double *sred;
+  PartialSums<W, 1> ps;
+  double rho, pap, rnorm2, bnorm2, rtol2, tol2, alpha0, beta0;
+  int done, iter, max_iter, stage;
+  __device__ __forceinline__ FoldAlpha(CgState *__restrict__ s, const double *__restrict__ part_pap, int n,
+                                       double *sr)
+      : st(s), sred(sr) {
+    ps.load(part_pap, nullptr, n);
+    const CgState *q = s + 1;
+    done = q->done; iter = q->iter; max_iter = q->max_iter; stage = q->done_stage;
+    rho = q->rho; pap = q->pap; rnorm2 = q->rnorm2; bnorm2 = q->bnorm2; rtol2 = q->rtol2; tol2 = q->tol2;
+    alpha0 = q->alpha; beta0 = q->beta;
+  }
+  __device__ __forceinline__ bool operator()(double *a, double *) {
+    double t;
+    ps.finish(sred, &t, nullptr);
+    int pending = 0;
+    if (done == kRunning) {
+      pap = t;
+      done = cg_alpha_done(t);
+      if (done == kRunning) {
+        alpha0 = rho / t;
+        pending = 1;
+      } else {
+        stage = 1;
+      }
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+      st->done = done; st->iter = iter; st->max_iter = max_iter; st->done_stage = stage; st->pending = pending;
+      st->rho = rho; st->pap = pap; st->rnorm2 = rnorm2; st->bnorm2 = bnorm2; st->rtol2 = rtol2; st->tol2 = tol2;
+      st->alpha = alpha0; st->beta = beta0;
+    }
+    *a = alpha0;
+    return done == kRunning;
+  }
+};
 
 // Outer step of the inner-outer CG: ||r||_c^2 of the true residual, the outer
 // count and the done flag.
@@ -593,6 +707,7 @@ __device__ inline void inner_init_step(CgState *st, const double *__restrict__ p
     st->max_iter = max_iter;
     st->rtol2 = rtol2;
     st->done_stage = 0;
+    st->pending = 0;
     st->rho = rho;
     st->bnorm2 = rr;
     st->rnorm2 = rr;

@@ -106,9 +106,37 @@ __device__ inline typename P::TC contraction_input(typename P::TC v) {
   }
 }
 
+// A double moved between lanes by the DPP pattern CTRL (every lane active).
+template <int CTRL>
+__device__ __forceinline__ double dpp_move(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, true);
+  return __hiloint2double(hi, lo);
+}
+
+// Sum over a wave, valid in every lane; every lane is active.  The butterfly
+// over lane distances 32, 16, 8, 4, 2, 1: each step adds the same two numbers
+// in both partners, so the order of the operands does not matter, and after
+// the step of distance 8 a rotation by 4 within the rows of 16 brings the
+// value of the lane at distance 4.  The moves are vector instructions (the
+// gfx950 row swaps and DPP); through the LDS crossbar (__shfl_xor, twelve
+// dependent operations of about 60 ns) a one-group step spent more time on
+// them than on its loads.
 __device__ inline double wave_sum(double v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+  {
+    const auto lo = __builtin_amdgcn_permlane32_swap(__double2loint(v), __double2loint(v), false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap(__double2hiint(v), __double2hiint(v), false, false);
+    v = __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+  }
+  {
+    const auto lo = __builtin_amdgcn_permlane16_swap(__double2loint(v), __double2loint(v), false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap(__double2hiint(v), __double2hiint(v), false, false);
+    v = __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+  }
+  v += dpp_move<0x128>(v);  // row_ror:8, distance 8
+  v += dpp_move<0x124>(v);  // row_ror:4, distance 4
+  v += dpp_move<0x4e>(v);   // quad_perm [2,3,0,1], distance 2
+  v += dpp_move<0xb1>(v);   // quad_perm [1,0,3,2], distance 1
   return v;
 }
 
@@ -246,6 +274,61 @@ __device__ inline void sum_partials2(const double *__restrict__ pa, const double
   const double y = ((c[0] + c[1]) + (c[2] + c[3])) + ((c[4] + c[5]) + (c[6] + c[7]));
   block_sum2<T>(x, y, sred, ta, tb);
 }
+
+// sum_partials (and sum_partials2 with NA = 2) of n <= kFinGroup partials by
+// a work-group of any size, W of its waves full: the additions of the
+// kFinGroup-thread work-group those run in, in the same order, so the same
+// bits; valid in every thread.  Wave w plays that group's waves w, w + W, ...
+// (those past the last partial add zeros and are left out); at this n each of
+// its threads has one partial.  load() issues the loads, so that they are in
+// flight with whatever the caller loads before finish().  sred holds 16 NA
+// doubles; the caller puts a barrier before it is written again.
+template <int W, int NA>
+struct PartialSums {
+  static constexpr int VW = kFinGroup / 64;
+  static constexpr int R = (VW + W - 1) / W;
+  static_assert(W >= 1 && W <= VW && (NA == 1 || NA == 2), "full waves of the work-group");
+  double v[NA][R];
+  int n;
+  __device__ __forceinline__ void load(const double *__restrict__ pa, const double *__restrict__ pb, int n_) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    n = n_;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const int q = (wave + r * W) * 64 + lane;
+      const bool ok = wave < W && q < n;
+      v[0][r] = ok ? pa[q] : 0.0;
+      if constexpr (NA == 2) v[1][r] = ok ? pb[q] : 0.0;
+    }
+  }
+  __device__ __forceinline__ void finish(double *sred, double *ta, double *tb) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if (wave < W) {
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const int vw = __builtin_amdgcn_readfirstlane(wave + r * W);
+        double a = 0.0, b = 0.0;
+        if (vw * 64 < n) {  // uniform in the wave
+          a = wave_sum(v[0][r]);
+          if constexpr (NA == 2) b = wave_sum(v[1][r]);
+        }
+        if (lane == 0 && vw < VW) {
+          sred[vw] = a;
+          if (NA == 2) sred[VW + vw] = b;
+        }
+      }
+    }
+    __syncthreads();
+    double x = 0.0, y = 0.0;
+#pragma unroll
+    for (int q = 0; q < VW; ++q) {
+      x += sred[q];
+      if (NA == 2) y += sred[VW + q];
+    }
+    *ta = x;
+    if (NA == 2) *tb = y;
+  }
+};
 
 // Work-groups are dispatched round-robin over the 8 XCDs; this maps the
 // launch index to a tile so that each XCD walks one contiguous range of

@@ -37,6 +37,16 @@ hipError_t launch_setup_geom(const Box &b, double amp, const double *D, const do
 // Inverse multiplicity c as an L-vector.
 hipError_t launch_fill_c(const Box &b, double *c, hipStream_t s);
 
+// The partials a folded iteration's launch sums for itself (cg_folded): the
+// last update's for the operator, the operator's for the update.  Empty: the
+// scalars are in the state.
+struct CgFold {
+  const double *part_rr = nullptr, *part_rz = nullptr;
+  int n_upd = 0;
+  const double *part_pap = nullptr;
+  int n_op = 0;
+};
+
 // w = A_L u.  With cg != null (a CG iteration) a prologue first finishes the
 // previous iteration, x += alpha p, then forms p <- Minv r + beta p (u is p,
 // updated in place), and the per-element sums of p.w go to part (E of them).
@@ -45,7 +55,7 @@ hipError_t launch_fill_c(const Box &b, double *c, hipStream_t s);
 // orders compiled at run time keep plain stores).
 hipError_t launch_ax_f64(const Box &b, int impl, const double *D, const double *G, double *u,
                          double *w, const double *r, const double *minv, double *x, CgState *cg,
-                         double *part, hipStream_t s, bool stream_w = false);
+                         double *part, hipStream_t s, bool stream_w = false, const CgFold &fold = {});
 
 // Low-precision operator (prec SEM_F32 or SEM_BF16): FP32 vectors, G stored
 // as float or bfloat16 bits, D as float (bfloat16-rounded in BF16 mode),
@@ -53,7 +63,7 @@ hipError_t launch_ax_f64(const Box &b, int impl, const double *D, const double *
 // correction e).  impl: an OpImpl.
 hipError_t launch_ax_lowp(const Box &b, int prec, int impl, const float *D, const void *G, float *u,
                           float *w, const float *r, const float *minv, float *x, CgState *cg,
-                          double *part, hipStream_t s, bool stream_w = false);
+                          double *part, hipStream_t s, bool stream_w = false, const CgFold &fold = {});
 // dst[i] = src[i] rounded to float (SEM_F32) or to bfloat16 bits (SEM_BF16).
 hipError_t launch_convert_g(int prec, int64_t n, const double *src, void *dst, hipStream_t s);
 
@@ -71,19 +81,25 @@ hipError_t launch_cg_init(const Box &b, const double *bvec, double *x, double *r
 // each).  Skipped when done.  variant: the update tile shape (upd_shape; the
 // orders compiled at run time have shape 0 only).
 hipError_t launch_cg_update(const Box &b, int variant, double *r, const double *w, const double *minv,
-                            CgState *st, double *part_rr, double *part_rz, hipStream_t s);
+                            CgState *st, double *part_rr, double *part_rz, hipStream_t s,
+                            const CgFold &fold = {});
 // One-group launches that finish the reductions and advance the scalars:
 // alpha = rho / <p, A p> (breakdown check), and after the update
-// iteration count, ||r||_c, rho, beta and the done flag.
+// iteration count, ||r||_c, rho, beta and the done flag.  A run of folded
+// iterations ends with launch_cg_beta_pending: the beta step of its last
+// update, if that is still to be done.
 hipError_t launch_cg_alpha(CgState *st, const double *part_pap, int64_t n, hipStream_t s);
 hipError_t launch_cg_beta(CgState *st, const double *part_rr, const double *part_rz, int64_t n,
                           hipStream_t s);
+hipError_t launch_cg_beta_pending(CgState *st, const double *part_rr, const double *part_rz, int64_t n,
+                                  hipStream_t s);
 // After the last iteration: x += alpha p if that iteration's update ran.
 hipError_t launch_cg_finish(const Box &b, double *x, const double *p, const CgState *st,
                             hipStream_t s);
 // FP32 update for the inner solver of the inner-outer CG.
 hipError_t launch_cg_update_f32(const Box &b, int variant, float *r, const float *w, const float *minv,
-                                CgState *st, double *part_rr, double *part_rz, hipStream_t s);
+                                CgState *st, double *part_rr, double *part_rz, hipStream_t s,
+                                const CgFold &fold = {});
 
 // Inner-outer CG steps.  inner_start: r_in = r / ||r||_c in FP32, e = p = 0,
 // then the inner state: tolerance rtol2 = eta^2 (relative), iteration cap,

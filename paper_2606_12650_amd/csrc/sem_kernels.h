@@ -39,12 +39,14 @@ struct OpCfg {
   static constexpr int MIN_WAVES = AxTile<N1>::kSplit ? SEM_OP_MIN_WAVES_SPLIT : SEM_OP_MIN_WAVES_COL;
 };
 
-template <int N1, class P, bool CG>
-__global__ void __launch_bounds__(OpCfg<N1>::THREADS, OpCfg<N1>::MIN_WAVES)
-    ax_kernel(int64_t E, const typename P::TC *__restrict__ Dg, const typename P::TG *__restrict__ G,
-              typename P::TV *u, typename P::TV *__restrict__ w, const typename P::TV *__restrict__ r,
-              const typename P::TV *__restrict__ minv, typename P::TV *__restrict__ x,
-              CgState *__restrict__ st, double *__restrict__ part) {
+template <int N1, class P, bool CG, class SC>
+__device__ __forceinline__ void ax_body(int64_t E, const typename P::TC *__restrict__ Dg,
+                                        const typename P::TG *__restrict__ G, typename P::TV *u,
+                                        typename P::TV *__restrict__ w,
+                                        const typename P::TV *__restrict__ r,
+                                        const typename P::TV *__restrict__ minv,
+                                        typename P::TV *__restrict__ x, const SC &scalars,
+                                        double *__restrict__ part) {
   using C = OpCfg<N1>;
   using TC = typename P::TC;
   __shared__ TC sD[N1 * N1];
@@ -52,26 +54,48 @@ __global__ void __launch_bounds__(OpCfg<N1>::THREADS, OpCfg<N1>::MIN_WAVES)
   __shared__ TC s2[C::EPB * AxTile<N1>::TILE];
   __shared__ TC s3[AxTile<N1>::kTiles == 3 ? C::EPB * AxTile<N1>::TILE : 1];
   __shared__ double sred[CG ? C::THREADS : 1];
-  double alpha = 0.0, beta = 0.0;
+  ax_tile<N1, C::EPB, P, CG, false, SC>(E, (int64_t)blockIdx.x * C::EPB, Dg, G, u, w, r, minv, x, scalars,
+                                        part, sD, s1, s2, s3, sred);
+}
+
+template <int N1, class P, bool CG>
+__global__ void __launch_bounds__(OpCfg<N1>::THREADS, OpCfg<N1>::MIN_WAVES)
+    ax_kernel(int64_t E, const typename P::TC *__restrict__ Dg, const typename P::TG *__restrict__ G,
+              typename P::TV *u, typename P::TV *__restrict__ w, const typename P::TV *__restrict__ r,
+              const typename P::TV *__restrict__ minv, typename P::TV *__restrict__ x,
+              CgState *__restrict__ st, double *__restrict__ part) {
+  GivenScalars sc{0.0, 0.0};
   if (CG) {
     if (st->done) return;  // uniform: converged solves skip all work
-    alpha = st->alpha;
-    beta = st->beta;
+    sc = GivenScalars{st->alpha, st->beta};
   }
-  ax_tile<N1, C::EPB, P, CG>(E, (int64_t)blockIdx.x * C::EPB, Dg, G, u, w, r, minv, x, alpha, beta,
-                             part, sD, s1, s2, s3, sred);
+  ax_body<N1, P, CG>(E, Dg, G, u, w, r, minv, x, sc, part);
+}
+
+// The CG operator of a folded iteration (cg_folded): the beta step of the
+// last update, whose n_upd partials are part_rr and part_rz, inside.
+template <int N1, class P>
+__global__ void __launch_bounds__(OpCfg<N1>::THREADS, OpCfg<N1>::MIN_WAVES)
+    ax_fold_kernel(int64_t E, const typename P::TC *__restrict__ Dg, const typename P::TG *__restrict__ G,
+                   typename P::TV *u, typename P::TV *__restrict__ w, const typename P::TV *__restrict__ r,
+                   const typename P::TV *__restrict__ minv, typename P::TV *__restrict__ x,
+                   CgState *__restrict__ st, double *__restrict__ part,
+                   const double *__restrict__ part_rr, const double *__restrict__ part_rz, int n_upd) {
+  __shared__ double sfold[2 * kFinGroup / 64];
+  const FoldBeta<OpCfg<N1>::THREADS / 64> sc(st, part_rr, part_rz, n_upd, sfold);
+  ax_body<N1, P, true>(E, Dg, G, u, w, r, minv, x, sc, part);
 }
 
 // The operator with the D contractions on the matrix cores (sem_ax_mfma.h):
 // ceil((N+1)^2 / 16) waves per element.
-template <int N1, class P, bool CG, bool SW>
+template <int N1, class P, bool CG, bool SW, class SC>
 __device__ __forceinline__ void ax_mfma_body(int64_t E, const typename P::TC *__restrict__ Dg,
                                              const typename P::TG *__restrict__ G,
                                              typename P::TV *u, typename P::TV *__restrict__ w,
                                              const typename P::TV *__restrict__ r,
                                              const typename P::TV *__restrict__ minv,
-                                             typename P::TV *__restrict__ x,
-                                             CgState *__restrict__ st, double *__restrict__ part) {
+                                             typename P::TV *__restrict__ x, const SC &scalars,
+                                             double *__restrict__ part) {
   using C = MfmaCfg<N1>;
   using TC = typename P::TC;
   __shared__ TC sD[N1 * N1];
@@ -79,14 +103,8 @@ __device__ __forceinline__ void ax_mfma_body(int64_t E, const typename P::TC *__
   __shared__ TC s2[C::EPB * AxTile<N1>::TILE];
   __shared__ TC s3[C::EPB * AxTile<N1>::TILE];
   __shared__ double sred[C::THREADS / 64];
-  double alpha = 0.0, beta = 0.0;
-  if (CG) {
-    if (st->done) return;  // uniform: converged solves skip all work
-    alpha = st->alpha;
-    beta = st->beta;
-  }
-  ax_tile_mfma<N1, C::EPB, P, CG, false, SW>(E, (int64_t)blockIdx.x * C::EPB, Dg, G, u, w, r, minv,
-                                             x, alpha, beta, part, sD, s1, s2, s3, sred);
+  ax_tile_mfma<N1, C::EPB, P, CG, false, SW, SC>(E, (int64_t)blockIdx.x * C::EPB, Dg, G, u, w, r, minv, x,
+                                                 scalars, part, sD, s1, s2, s3, sred);
 }
 
 template <int N1, class P, bool CG>
@@ -96,7 +114,26 @@ __global__ void __launch_bounds__(MfmaCfg<N1>::THREADS, (mfma_waves_per_simd<N1,
                    typename P::TV *__restrict__ w, const typename P::TV *__restrict__ r,
                    const typename P::TV *__restrict__ minv, typename P::TV *__restrict__ x,
                    CgState *__restrict__ st, double *__restrict__ part) {
-  ax_mfma_body<N1, P, CG, false>(E, Dg, G, u, w, r, minv, x, st, part);
+  GivenScalars sc{0.0, 0.0};
+  if (CG) {
+    if (st->done) return;  // uniform: converged solves skip all work
+    sc = GivenScalars{st->alpha, st->beta};
+  }
+  ax_mfma_body<N1, P, CG, false>(E, Dg, G, u, w, r, minv, x, sc, part);
+}
+
+// As ax_fold_kernel.
+template <int N1, class P>
+__global__ void __launch_bounds__(MfmaCfg<N1>::THREADS, (mfma_waves_per_simd<N1, P, true>()))
+    ax_mfma_fold_kernel(int64_t E, const typename P::TC *__restrict__ Dg,
+                        const typename P::TG *__restrict__ G, typename P::TV *u,
+                        typename P::TV *__restrict__ w, const typename P::TV *__restrict__ r,
+                        const typename P::TV *__restrict__ minv, typename P::TV *__restrict__ x,
+                        CgState *__restrict__ st, double *__restrict__ part,
+                        const double *__restrict__ part_rr, const double *__restrict__ part_rz, int n_upd) {
+  __shared__ double sfold[2 * kFinGroup / 64];
+  const FoldBeta<MfmaCfg<N1>::THREADS / 64> sc(st, part_rr, part_rz, n_upd, sfold);
+  ax_mfma_body<N1, P, true, false>(E, Dg, G, u, w, r, minv, x, sc, part);
 }
 
 // The element-local sem_ax, whose result goes to the caller as it is (no
@@ -107,7 +144,7 @@ __global__ void __launch_bounds__(MfmaCfg<N1>::THREADS, (mfma_waves_per_simd<N1,
     ax_mfma_local_kernel(int64_t E, const typename P::TC *__restrict__ Dg,
                          const typename P::TG *__restrict__ G, typename P::TV *u,
                          typename P::TV *__restrict__ w) {
-  ax_mfma_body<N1, P, false, true>(E, Dg, G, u, w, nullptr, nullptr, nullptr, nullptr, nullptr);
+  ax_mfma_body<N1, P, false, true>(E, Dg, G, u, w, nullptr, nullptr, nullptr, GivenScalars{0.0, 0.0}, nullptr);
 }
 
 // Metric setup: coordinates of the (deformed) box mesh, isoparametric
@@ -307,11 +344,33 @@ __global__ void __launch_bounds__((UpdTile<N1, TV, V>::BLOCK))
   __shared__ double sred[2 * (UpdTile<N1, TV, V>::BLOCK / 64)];
   __shared__ double sA[UpdTile<N1, TV, V>::LDS];
   if (st->done) return;
-  const double alpha = st->alpha;
+  const GivenScalars sc{st->alpha, 0.0};
   const int64_t tile = xcd_tile(ntiles);
   TileSums t{0.0, 0.0};
   if (tile < ntiles)
-    t = cg_update_tile<N1, TV, V>(b, tile, r, w, minv, alpha, sA, sred, (int)threadIdx.x);
+    t = cg_update_tile<N1, TV, V>(b, tile, r, w, minv, sc, sA, sred, (int)threadIdx.x);
+  if (threadIdx.x == 0) {
+    part_rr[tile] = t.a;
+    part_rz[tile] = t.b;
+  }
+}
+
+// The CG update of a folded iteration (cg_folded), on the default tile: the
+// alpha step from the operator's n_op partials part_pap inside.
+template <int N1, typename TV>
+__global__ void __launch_bounds__((UpdTile<N1, TV>::BLOCK))
+    cg_update_fold_kernel(Box b, int64_t ntiles, TV *__restrict__ r, const TV *__restrict__ w,
+                          const TV *__restrict__ minv, CgState *__restrict__ st,
+                          double *__restrict__ part_rr, double *__restrict__ part_rz,
+                          const double *__restrict__ part_pap, int n_op) {
+  constexpr int W = UpdTile<N1, TV>::BLOCK / 64;
+  __shared__ double sred[2 * W];
+  __shared__ double sfold[kFinGroup / 64];  // not sred: no barrier follows its last read
+  __shared__ double sA[UpdTile<N1, TV>::LDS];
+  const int64_t tile = xcd_tile(ntiles);
+  if (tile >= ntiles) return;
+  const FoldAlpha<W> sc(st, part_pap, n_op, sfold);
+  const TileSums t = cg_update_tile<N1, TV>(b, tile, r, w, minv, sc, sA, sred, (int)threadIdx.x);
   if (threadIdx.x == 0) {
     part_rr[tile] = t.a;
     part_rz[tile] = t.b;

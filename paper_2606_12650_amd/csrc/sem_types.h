@@ -71,7 +71,36 @@ struct CgState {
   double bnorm2;  // <b, b>_c
   double rtol2;   // rtol^2 (< 0: fixed-iteration mode, never converges)
   double tol2;    // rtol2 * bnorm2
+  int pending;    // folded iterations: the beta step of the last update is still to be done
+  int reserved;
 };
+
+// A solve holds two states side by side.  Iterations with their scalar steps
+// in launches of their own use the first.  Folded iterations (cg_folded) hand
+// the scalars back and forth: the operator kernel reads the first and writes
+// the second, the update kernel reads the second and writes the first, so no
+// launch reads what another of its work-groups may be writing.
+constexpr int kCgStates = 2;
+
+// Threads of the one-group launches that finish a reduction.
+constexpr int kFinGroup = 1024;
+
+// Whether a solve with these partial counts folds its scalar steps into the
+// operator and update kernels, every work-group summing the partials itself
+// (sem_device.h, PartialSums), instead of running them in two one-group
+// launches per iteration.  Such a launch costs about 3.5 us however small the
+// mesh; the folded sum hides behind the tile's own loads while each thread has
+// one partial of an array, i.e. up to kFinGroup of them.  us per iteration on
+// MI355X, separate -> folded: FP64 N = 7, E = 64 / 512 / 1024 15.5 / 17.2 /
+// 23.6 -> 11.5 / 13.1 / 19.1; FP32 N = 7, E = 64 / 1024 14.1 / 18.4 -> 10.5 /
+// 14.2; N = 4, E = 64 14.7 -> 12.4; N = 11, E = 1024 57.7 -> 53.0.  With two
+// partials per thread E = 2048 gains (36.9 -> 33.2 at N = 7) but every smaller
+// mesh pays about 0.3 us for their registers, and with four E = 4096 at N = 9
+// and 11 loses 5-10 %.  Only the default update tile of the built orders has
+// the folded form.
+inline bool cg_folded(const Box &b, int upd_variant, int64_t n_op, int64_t n_upd) {
+  return b.N <= kMaxOrder && upd_variant == 0 && n_op <= kFinGroup && n_upd <= kFinGroup;
+}
 
 // Launch shapes of the element kernels (shared by host sizing code).
 int ax_elements_per_block(int N);

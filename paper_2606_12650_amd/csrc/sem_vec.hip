@@ -44,6 +44,15 @@ __global__ void __launch_bounds__(kFinThreads)
   cg_beta_step(st, part_rr, part_rz, n, sred);
 }
 
+// The beta step a run of folded iterations leaves (none: the solve had
+// stopped, or an earlier launch took it).
+__global__ void __launch_bounds__(kFinThreads)
+    cg_beta_pending_kernel(CgState *st, const double *__restrict__ part_rr,
+                           const double *__restrict__ part_rz, int64_t n) {
+  __shared__ double sred[2 * (kFinThreads / 64)];
+  if (st->done == kRunning && st->pending) cg_beta_step(st, part_rr, part_rz, n, sred);
+}
+
 __global__ void __launch_bounds__(kFinThreads)
     outer_finish_kernel(CgState *st, const double *__restrict__ part, int64_t n) {
   __shared__ double sred[2 * (kFinThreads / 64)];
@@ -190,30 +199,39 @@ inline dim3 vec_grid(int64_t n) { return dim3((unsigned)vec_num_blocks(n)); }
 // The update of order N1 - 1 with tile shape V (upd_shape).
 template <int N1, typename TV, int V>
 hipError_t update_launch(const Box &b, TV *r, const TV *w, const TV *minv, CgState *st,
-                         double *part_rr, double *part_rz, hipStream_t s) {
+                         double *part_rr, double *part_rz, hipStream_t s, const CgFold &fold) {
   constexpr bool f64 = sizeof(TV) == 8;
   if constexpr (!upd_variant_exists(N1, f64, V)) {
     return hipErrorInvalidValue;
   } else {
-    hipLaunchKernelGGL((cg_update_kernel<N1, TV, V>), dim3((unsigned)upd_grid_blocks(b, f64, V)),
-                       dim3(UpdTile<N1, TV, V>::BLOCK), 0, s, b, upd_num_tiles(b, f64, V), r, w,
-                       minv, st, part_rr, part_rz);
+    if (fold.n_op > 0) {
+      if constexpr (V == 0)
+        hipLaunchKernelGGL((cg_update_fold_kernel<N1, TV>), dim3((unsigned)upd_grid_blocks(b, f64)),
+                           dim3(UpdTile<N1, TV>::BLOCK), 0, s, b, upd_num_tiles(b, f64), r, w, minv, st,
+                           part_rr, part_rz, fold.part_pap, fold.n_op);
+      else
+        return hipErrorInvalidValue;
+    } else {
+      hipLaunchKernelGGL((cg_update_kernel<N1, TV, V>), dim3((unsigned)upd_grid_blocks(b, f64, V)),
+                         dim3(UpdTile<N1, TV, V>::BLOCK), 0, s, b, upd_num_tiles(b, f64, V), r, w,
+                         minv, st, part_rr, part_rz);
+    }
     return hipGetLastError();
   }
 }
 
 template <typename TV>
 hipError_t update_typed(const Box &b, int variant, TV *r, const TV *w, const TV *minv, CgState *st,
-                        double *part_rr, double *part_rz, hipStream_t s) {
+                        double *part_rr, double *part_rz, hipStream_t s, const CgFold &fold) {
   if (b.E() == 0) return hipSuccess;
   switch (b.N) {
 #define UCASE(n_)                                                                                \
   case n_:                                                                                       \
     switch (variant) {                                                                           \
-      case 0: return update_launch<n_ + 1, TV, 0>(b, r, w, minv, st, part_rr, part_rz, s);       \
-      case 1: return update_launch<n_ + 1, TV, 1>(b, r, w, minv, st, part_rr, part_rz, s);       \
-      case 2: return update_launch<n_ + 1, TV, 2>(b, r, w, minv, st, part_rr, part_rz, s);       \
-      case 3: return update_launch<n_ + 1, TV, 3>(b, r, w, minv, st, part_rr, part_rz, s);       \
+      case 0: return update_launch<n_ + 1, TV, 0>(b, r, w, minv, st, part_rr, part_rz, s, fold); \
+      case 1: return update_launch<n_ + 1, TV, 1>(b, r, w, minv, st, part_rr, part_rz, s, fold); \
+      case 2: return update_launch<n_ + 1, TV, 2>(b, r, w, minv, st, part_rr, part_rz, s, fold); \
+      case 3: return update_launch<n_ + 1, TV, 3>(b, r, w, minv, st, part_rr, part_rz, s, fold); \
       default: return hipErrorInvalidValue;                                                      \
     }
     UCASE(1) UCASE(2) UCASE(3) UCASE(4) UCASE(5) UCASE(6)
@@ -336,18 +354,26 @@ hipError_t launch_cg_beta(CgState *st, const double *part_rr, const double *part
   return hipGetLastError();
 }
 
+hipError_t launch_cg_beta_pending(CgState *st, const double *part_rr, const double *part_rz, int64_t n,
+                                  hipStream_t s) {
+  hipLaunchKernelGGL(cg_beta_pending_kernel, dim3(1), dim3(kFinThreads), 0, s, st, part_rr, part_rz, n);
+  return hipGetLastError();
+}
+
 hipError_t launch_cg_update(const Box &b, int variant, double *r, const double *w, const double *minv,
-                            CgState *st, double *part_rr, double *part_rz, hipStream_t s) {
+                            CgState *st, double *part_rr, double *part_rz, hipStream_t s,
+                            const CgFold &fold) {
   if (rtc_order(b.N)) {
     if (variant != 0) return hipErrorInvalidValue;
     return b.E() == 0 ? hipSuccess : rtc_cg_update(b, r, w, minv, st, part_rr, part_rz, s);
   }
-  return update_typed<double>(b, variant, r, w, minv, st, part_rr, part_rz, s);
+  return update_typed<double>(b, variant, r, w, minv, st, part_rr, part_rz, s, fold);
 }
 
 hipError_t launch_cg_update_f32(const Box &b, int variant, float *r, const float *w, const float *minv,
-                                CgState *st, double *part_rr, double *part_rz, hipStream_t s) {
-  return update_typed<float>(b, variant, r, w, minv, st, part_rr, part_rz, s);
+                                CgState *st, double *part_rr, double *part_rz, hipStream_t s,
+                                const CgFold &fold) {
+  return update_typed<float>(b, variant, r, w, minv, st, part_rr, part_rz, s, fold);
 }
 
 hipError_t launch_cg_finish(const Box &b, double *x, const double *p, const CgState *st,
