@@ -227,7 +227,17 @@ struct LinItems {
   }
 };
 
-template <int N1, typename TV, class SC>
+// The store of the new r: non-temporal on vectors larger than the last-level
+// cache (upd_streams_r).
+template <bool NTS, typename TV>
+__device__ __forceinline__ void store_r(TV *p, TV v) {
+  if constexpr (NTS)
+    st_once(p, v);
+  else
+    *p = v;
+}
+
+template <int N1, typename TV, bool NTS, class SC>
 __device__ inline TileSums cg_update_tile_linear(const Box &b, int64_t tile, TV *__restrict__ r,
                                                  const TV *__restrict__ w,
                                                  const TV *__restrict__ minv, SC scalars,
@@ -285,7 +295,7 @@ __device__ inline TileSums cg_update_tile_linear(const Box &b, int64_t tile, TV 
   }
 #pragma unroll
   for (int u = 0; u < kVecItems; ++u)
-    if (upd[u]) r[P.raw0 + (uint32_t)(u * kVecThreads)] = rnew[u];
+    if (upd[u]) store_r<NTS>(r + P.raw0 + (uint32_t)(u * kVecThreads), rnew[u]);
   TileSums t;
   block_sum2<kVecThreads>(rr, rz, sred, &t.a, &t.b);
   return t;
@@ -389,14 +399,14 @@ __device__ inline void column_copy_sums(const ColumnPos<N1, TV, V> &p, const TV 
   for (int kk = 0; kk < KN; ++kk) S[kk] = p.hx ? A[kk] + X[kk] : A[kk];
 }
 
-template <int N1, typename TV, int V = 0, class SC>
+template <int N1, typename TV, int V = 0, bool NTS = false, class SC>
 __device__ inline TileSums cg_update_tile(const Box &b, int64_t tile, TV *__restrict__ r,
                                           const TV *__restrict__ w, const TV *__restrict__ minv,
                                           SC scalars, double *sA, double *sred,
                                           int tid) {
   using U = UpdTile<N1, TV, V>;
   if constexpr (U::LINEAR)
-    return cg_update_tile_linear<N1, TV>(b, tile, r, w, minv, scalars, sred, tid);
+    return cg_update_tile_linear<N1, TV, NTS>(b, tile, r, w, minv, scalars, sred, tid);
   constexpr int N = U::N, COLS = U::COLS, KN = U::KN;
   const ColumnPos<N1, TV, V> p(b, tile, tid);
   // the copies of w are summed, and r updated, in the vector type (FP64, or
@@ -419,7 +429,7 @@ __device__ inline TileSums cg_update_tile(const Box &b, int64_t tile, TV *__rest
     const int k = p.kb + kk;
     if (p.live && k < p.kend && !p.boundary(b, k)) {
       const TV rt = rv[kk] - alpha_v * S[kk];
-      r[p.col0 + (int64_t)k * COLS] = rt;
+      store_r<NTS>(r + p.col0 + (int64_t)k * COLS, rt);
       const double c = p.inv_mult(b, k);
       const double rd = (double)rt;
       rr += c * rd * rd;

@@ -341,6 +341,15 @@ __device__ inline int64_t xcd_tile(int64_t ntiles) {
   return (b % kNumXcd) * per + b / kNumXcd;
 }
 
+// The tile of this work-group in a launch of tile_grid(ntiles) (a value past
+// the last tile: none).
+__device__ inline int64_t chunk_tile(int64_t ntiles) {
+  if (!tiles_chunked(ntiles)) return xcd_tile(ntiles);
+  const int64_t x = blockIdx.x % kNumXcd, j = blockIdx.x / kNumXcd;
+  const int64_t t = (j / kTileChunk * kNumXcd + x) * kTileChunk + j % kTileChunk;
+  return t < ntiles ? ntiles - 1 - t : t;
+}
+
 // Position of an element-local node of a box mesh.
 template <int N1>
 struct Node {

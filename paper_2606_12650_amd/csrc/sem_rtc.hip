@@ -435,7 +435,7 @@ hipError_t rtc_gather(const Box &b, const double *wl, double *out, int mode, hip
   Box bb = b;
   int64_t L = b.L(), nt = vec_num_blocks(L);
   void *args[] = {&bb, &L, &nt, &wl, &out};
-  return launch(b.N, k, dim3((unsigned)vec_grid_blocks(L)), dim3(kVecThreads), s, args);
+  return launch(b.N, k, dim3((unsigned)tile_grid(nt)), dim3(kVecThreads), s, args);
 }
 
 hipError_t rtc_cg_init(const Box &b, const double *bvec, double *x, double *r, double *p,

@@ -113,6 +113,25 @@ inline int64_t vec_num_blocks(int64_t n) { return (n + kVecTile - 1) / kVecTile;
 // tiles padded to a multiple of the XCD count.
 inline int64_t vec_grid_blocks(int64_t n) { return 8 * ((vec_num_blocks(n) + 7) / 8); }
 
+// Tile order of the kernels that read the operator's element-local result
+// with its copies (the CG update, the gathers).  From kChunkTiles tiles on they
+// walk the mesh backwards, in chunks of kTileChunk consecutive tiles per XCD
+// (sem_device.h, chunk_tile): the operator walks it forwards, so what it wrote
+// last, and the 256 MB last-level cache still holds, is read first, and the
+// other way round for r at the next operator launch; a chunk keeps the x
+// copies, and most y copies, in one XCD's L2.  Fewer tiles keep one contiguous
+// range per XCD (about one launch wave: the order does not matter, and every
+// XCD has its share).  Measured on MI355X, 32^3 box, one contiguous range per
+// XCD forwards -> chunks backwards, us: FP64 update N = 7 101 -> 96, N = 11
+// 407 -> 369 (and the operator after it 1012 -> 993); FP32 N = 11 197 -> 191.
+constexpr int kTileChunk = 32;
+constexpr int64_t kChunkTiles = 4096;
+__host__ __device__ constexpr bool tiles_chunked(int64_t ntiles) { return ntiles >= kChunkTiles; }
+inline int64_t tile_grid(int64_t ntiles) {
+  const int64_t m = tiles_chunked(ntiles) ? 8 * kTileChunk : 8;
+  return m * ((ntiles + m - 1) / m);
+}
+
 // Tiles of the CG update (the gather-scatter pulled into r -= alpha w) are
 // element-aligned: upd_ept consecutive elements with upd_ks threads per
 // (i, j) column over all planes.  Up to order 7 a tile fills 256 threads; at
@@ -140,7 +159,24 @@ struct UpdShape {
   int ks, ept, kp;
 };
 constexpr int kUpdVariants = 4;
+
+// The shape of the sem_ax gathers (assembled and masked), beside the update's
+// candidates.  Up to order 8 the update's default; above, where the gather has
+// neither r nor the diagonal to load, more elements per tile (the x copies
+// inside it come from LDS) and plane ranges beat the linear tile.  us per
+// masked gather on MI355X, linear -> this: FP64 N = 9, 5083 elements 20.4 ->
+// 17.3; N = 10, 4096 21.0 -> 18.1; N = 11, 21952 92 -> 83; N = 12, 1000 11.1 ->
+// 9.7; FP32 N = 11, 4096 26.4 -> 24.7; N = 12, 1728 17.3 -> 13.3.  The Jacobi
+// set-up keeps the update's tile (the diagonal's sums in one order for good).
+constexpr int kGatherShape = kUpdVariants;
 __host__ __device__ constexpr UpdShape upd_shape(int n1, bool f64, int v) {
+  if (v == kGatherShape) {
+    if (n1 == 10) return UpdShape{1, 5, 2};
+    if (n1 == 11) return UpdShape{1, 4, 3};
+    if (n1 == 12) return UpdShape{1, 3, 3};
+    if (n1 == 13) return UpdShape{1, 3, f64 ? 3 : 4};
+    v = 0;
+  }
   if (v == 0)
     return upd_linear(n1, f64) ? UpdShape{0, 0, 0} : UpdShape{upd_ks(n1, f64), upd_ept(n1, f64), 1};
   if (v < 0 || v >= kUpdVariants) return UpdShape{-1, 0, 0};
@@ -179,10 +215,15 @@ inline int64_t upd_num_tiles(const Box &b, bool f64, int v = 0) {
   if (sh.ks == 0) return vec_num_blocks(b.L());
   return (b.E() + sh.ept - 1) / sh.ept * sh.kp;
 }
-// Launch size of the update (a multiple of the XCD count).
-inline int64_t upd_grid_blocks(const Box &b, bool f64, int v = 0) {
-  return 8 * ((upd_num_tiles(b, f64, v) + 7) / 8);
-}
+// Launch size of the update.
+inline int64_t upd_grid_blocks(const Box &b, bool f64, int v = 0) { return tile_grid(upd_num_tiles(b, f64, v)); }
+
+// Whether the update writes r with non-temporal stores: vectors larger than
+// the last-level cache.  There a plain store displaces the part of w the
+// update has yet to read (FP64 N = 11, 453 MB a vector: 369 -> 350 us); a
+// vector that fits is wanted there by the next operator launch (N = 7, 134 MB:
+// with non-temporal stores the operator went from 257 to 270 us).
+inline bool upd_streams_r(const Box &b, bool f64) { return b.L() * (f64 ? 8 : 4) > (int64_t)256 << 20; }
 // Partials a solve's streaming reductions need room for (every candidate
 // update tile of both vector types).
 inline int64_t stream_partials(const Box &b) {

@@ -211,6 +211,10 @@ hipError_t update_launch(const Box &b, TV *r, const TV *w, const TV *minv, CgSta
                            part_rr, part_rz, fold.part_pap, fold.n_op);
       else
         return hipErrorInvalidValue;
+    } else if (V == 0 && upd_streams_r(b, f64)) {
+      hipLaunchKernelGGL((cg_update_stream_kernel<N1, TV>), dim3((unsigned)upd_grid_blocks(b, f64)),
+                         dim3(UpdTile<N1, TV>::BLOCK), 0, s, b, upd_num_tiles(b, f64), r, w, minv, st, part_rr,
+                         part_rz);
     } else {
       hipLaunchKernelGGL((cg_update_kernel<N1, TV, V>), dim3((unsigned)upd_grid_blocks(b, f64, V)),
                          dim3(UpdTile<N1, TV, V>::BLOCK), 0, s, b, upd_num_tiles(b, f64, V), r, w,
@@ -280,17 +284,19 @@ inline dim3 xcd_vec_grid(int64_t n) { return dim3((unsigned)vec_grid_blocks(n));
     default: return hipErrorInvalidValue;                               \
   }
 
-// The gather on the tiles the CG update of this order and precision uses.
+// The gather: the Jacobi set-up on the tiles the CG update of this order and
+// type uses, sem_ax on its own (kGatherShape).
 template <int N1, int MODE, typename T>
 void gather_launch(const Box &b, const T *wl, T *out, hipStream_t s) {
-  if constexpr (UpdTile<N1, T>::LINEAR) {
+  constexpr int V = MODE == kGatherInverse ? 0 : kGatherShape;
+  if constexpr (UpdTile<N1, T, V>::LINEAR) {
     const int64_t L = b.L();
-    hipLaunchKernelGGL((gather_kernel<N1, MODE, T>), xcd_vec_grid(L), dim3(kVecThreads), 0, s, b, L,
-                       vec_num_blocks(L), wl, out);
+    hipLaunchKernelGGL((gather_kernel<N1, MODE, T>), dim3((unsigned)tile_grid(vec_num_blocks(L))),
+                       dim3(kVecThreads), 0, s, b, L, vec_num_blocks(L), wl, out);
   } else {
     const bool f64 = sizeof(T) == 8;
-    hipLaunchKernelGGL((gather_col_kernel<N1, MODE, T>), dim3((unsigned)upd_grid_blocks(b, f64)),
-                       dim3(UpdTile<N1, T>::BLOCK), 0, s, b, upd_num_tiles(b, f64), wl, out);
+    hipLaunchKernelGGL((gather_col_kernel<N1, MODE, T, V>), dim3((unsigned)upd_grid_blocks(b, f64, V)),
+                       dim3(UpdTile<N1, T, V>::BLOCK), 0, s, b, upd_num_tiles(b, f64, V), wl, out);
   }
 }
 
