@@ -325,21 +325,23 @@ int sem_export(sem_ctx *ctx, int field, double *dst_dev, void *stream);
 
 /* ------------------------------------------------------------------ batches
  * Many independent solves (different meshes, orders 1..11, FP64 or mixed
- * precision) advance together: each batched step runs one CG iteration of
- * every active solve.  A one-work-group schedule kernel first builds, on the
- * device, compact work lists of the solves that have operator work in each
- * (arithmetic class, order) bin, of their CG update tiles per order and of
- * the streaming tiles of the solves in an outer-residual phase; then one
- * persistent operator launch per bin in use and one update launch per order
- * and family in use (each compiled for its order), one work-group per solve
- * for the scalars, and the finishing launches over lists rebuilt after the
- * scalars have set each solve's phase.  Every solve's arithmetic and
- * reduction order are those of sem_cg, so an FP64 solve gives the same bits
- * in a batch as alone.
+ * precision) advance together: each batched iteration runs one CG iteration of
+ * every active solve.  A one-work-group schedule kernel builds, on the device,
+ * compact work lists of the solves that have operator work in each (arithmetic
+ * class, order) bin, of their CG update tiles per order and of the streaming
+ * tiles of the solves in an outer-residual phase; an iteration is then one
+ * persistent operator launch per bin in use, one update launch per order and
+ * family in use (each compiled for its order) and one work-group per solve for
+ * the scalars.  After every tenth iteration of a step, and after its last, the
+ * solves that have stopped go through the phases they owe (the last update of
+ * x; outer correction, true residual and inner restart of a mixed solve) and
+ * the lists are rebuilt.  Every solve's arithmetic and reduction order are
+ * those of sem_cg, so an FP64 solve gives the same bits in a batch as alone.
  * Solves join and leave between steps (continuous batching); the step's
- * graph is captured again only when the set of bins in use or the tiles
- * change.  The batch holds no memory of its own on the device beyond its
- * workspace; each solve keeps its state in its sem_ctx workspace.  Calls on
+ * graph is captured again only when the set of bins in use, the tiles or the
+ * launch sizes (powers of two of the work the occupied slots can have) change.
+ * The batch holds no memory of its own on the device beyond its workspace; each
+ * solve keeps its state in its sem_ctx workspace.  Calls on
  * one batch must not overlap. */
 typedef struct sem_batch sem_batch;
 

@@ -795,6 +795,7 @@ struct sem_batch {
   hipStream_t graph_stream;
   int graph_iters;
   uint64_t graph_bins;
+  semk::BatchBounds graph_bounds;
   semk::BatchTiles graph_tiles;
 };
 
@@ -838,6 +839,31 @@ uint64_t batch_bins(const sem_batch *B) {
   return m;
 }
 
+// Items of the operator bins and update lists the occupied slots can have.
+semk::BatchBounds batch_bounds(const sem_batch *B) {
+  int64_t op[semk::kBatchBins] = {}, upd[2][semk::kBatchOrders + 1] = {};
+  for (int q = 0; q < B->max_slots; ++q) {
+    if (!B->ctx[q]) continue;
+    const semk::BatchSlot &S = B->slots[q];
+    const int cls = S.mixed == 0 ? 0 : S.mixed == SEM_F32 ? 1 : 2;
+    auto items = [&](int c) { return (S.E + B->tiles.epb[c][S.N] - 1) / B->tiles.epb[c][S.N]; };
+    op[semk::batch_bin(cls, S.N)] += items(cls);
+    if (S.mixed) op[semk::batch_bin(3, S.N)] += items(3);
+    upd[S.mixed ? 1 : 0][S.N] += S.utiles;
+  }
+  auto pow2 = [](int64_t n) {
+    int64_t p = n > 0 ? 1 : 0;
+    while (p < n && p < (1 << 30)) p <<= 1;
+    return (int)p;
+  };
+  semk::BatchBounds b;
+  std::memset(&b, 0, sizeof(b));
+  for (int k = 0; k < semk::kBatchBins; ++k) b.op[k] = pow2(op[k]);
+  for (int f = 0; f < 2; ++f)
+    for (int N = 1; N <= semk::kBatchOrders; ++N) b.upd[f][N] = pow2(upd[f][N]);
+  return b;
+}
+
 }  // namespace
 
 extern "C" {
@@ -879,6 +905,7 @@ int sem_batch_create(int max_slots, void *dev_ws, size_t ws_bytes, void *stream,
   B->graph_stream = nullptr;
   B->graph_iters = 0;
   B->graph_bins = 0;
+  std::memset(&B->graph_bounds, 0, sizeof(B->graph_bounds));
   std::memset(&B->graph_tiles, 0, sizeof(B->graph_tiles));
   e = hipMemcpyAsync(B->d_slots, B->slots.data(), max_slots * sizeof(semk::BatchSlot),
                      hipMemcpyHostToDevice, s);
@@ -1003,17 +1030,16 @@ int sem_batch_step(sem_batch *B, int iters, void *stream) {
   if (iters < 1) return fail(SEM_ERR_ARG, "sem_batch_step: iters must be >= 1");
   hipStream_t s = (hipStream_t)stream;
   const uint64_t bins = batch_bins(B);
+  const semk::BatchBounds bounds = batch_bounds(B);
   const bool same = B->graph && B->graph_stream == s && B->graph_iters == iters &&
-                    B->graph_bins == bins &&
+                    B->graph_bins == bins && std::memcmp(&B->graph_bounds, &bounds, sizeof(bounds)) == 0 &&
                     std::memcmp(&B->graph_tiles, &B->tiles, sizeof(B->tiles)) == 0;
   if (s != nullptr && !same) {
     if (B->graph) (void)hipGraphExecDestroy(B->graph);
     B->graph = nullptr;
     if (hipStreamBeginCapture(s, hipStreamCaptureModeRelaxed) == hipSuccess) {
-      hipError_t e = hipSuccess;
-      for (int it = 0; it < iters && e == hipSuccess; ++it)
-        e = semk::launch_batch_iteration(B->d_slots, B->max_slots, B->sched, B->tiles, bins,
-                                         B->d_status, s);
+      hipError_t e = semk::launch_batch_step(B->d_slots, B->max_slots, B->sched, B->tiles, bins, bounds,
+                                             B->d_status, iters, s);
       hipGraph_t g = nullptr;
       hipError_t e2 = hipStreamEndCapture(s, &g);
       if (e != hipSuccess || e2 != hipSuccess) {
@@ -1028,6 +1054,7 @@ int sem_batch_step(sem_batch *B, int iters, void *stream) {
       B->graph_stream = s;
       B->graph_iters = iters;
       B->graph_bins = bins;
+      B->graph_bounds = bounds;
       B->graph_tiles = B->tiles;
     } else {
       (void)hipGetLastError();
@@ -1037,9 +1064,8 @@ int sem_batch_step(sem_batch *B, int iters, void *stream) {
       B->graph_bins == bins) {
     SEM_HIP(hipGraphLaunch(B->graph, s));
   } else {
-    for (int it = 0; it < iters; ++it)
-      SEM_HIP(semk::launch_batch_iteration(B->d_slots, B->max_slots, B->sched, B->tiles, bins,
-                                           B->d_status, s));
+    SEM_HIP(semk::launch_batch_step(B->d_slots, B->max_slots, B->sched, B->tiles, bins, bounds, B->d_status,
+                                    iters, s));
   }
   return SEM_OK;
 }

@@ -1,18 +1,28 @@
 // Batched Jacobi-PCG: many independent solves of different sizes and orders
 // advance together, one CG iteration per batched step.
 //
-// Every batched iteration starts with a one-work-group schedule kernel that
-// reads the solves' phases on the device and writes compact work lists: for
-// each (arithmetic class, order) bin the solves with operator work in it and
-// the prefix sums of their item counts, and the same for the streaming tiles
-// of every unfinished solve.  The operator work then runs in one persistent
-// launch per bin, each compiled for its order (work-group size, LDS and
-// registers of the single-solve kernel of that order), so a bin of small
+// A one-work-group schedule kernel reads the solves' phases on the device and
+// writes compact work lists: for each (arithmetic class, order) bin the solves
+// with operator work in it and the prefix sums of their item counts, the same
+// for the update tiles of each order and family, and the streaming tiles of
+// the solves in an outer-residual phase.  The work then runs in one persistent
+// launch per list in use, each compiled for its order (work-group size, LDS
+// and registers of the single-solve kernel of that order), so a list of small
 // elements is not held to the resources of the largest order.  Each work-group
-// takes a contiguous range of its bin's items and finds their solves by
-// searching the prefix sums; finished solves and idle phases take no items.
-// The per-solve scalars run one work-group per solve, the streaming launches
-// walk the streaming list in XCD-contiguous ranges.
+// takes a contiguous range of its list's items and finds their solves by
+// searching the prefix sums; a launch takes no more work-groups than the
+// batch's own solves can use (BatchBounds: the full persistent grid of an
+// almost empty list cost 5-10 us a launch).
+//
+// The lists hold for up to kBatchPhaseEvery iterations: a solve that stops in
+// between is skipped by the kernels that walk them.  Only then do the phases
+// advance (finishing an FP64 solve; outer correction, true residual and inner
+// restart of a mixed one) and the lists get rebuilt.  Doing that in every
+// iteration took 12 of 22 launches of a batch of five orders, most of them over
+// empty lists, 95 of 200 us; now a stopped solve waits for five iterations on
+// average, four to nine times in a solve of several hundred.  24 solves of
+// 64..1024 elements in FP32: 253 -> 134 ms; 64 of 64..4096: 589 -> 434 ms (FP64
+// 671 -> 625).
 //
 // Every item is computed by the same device functions as a single solve
 // (sem_ax_tile.h, sem_cg_dev.h) and each solve's reductions are summed in
@@ -205,8 +215,7 @@ __global__ void __launch_bounds__(kSchedThreads)
   }
 }
 
-// The two finishing lists, rebuilt after the beta launch has set this
-// iteration's phases: FP64 solves that stopped (x owes alpha p) and mixed
+// The two finishing lists, rebuilt when the phases advance: FP64 solves that stopped (x owes alpha p) and mixed
 // solves whose inner solve ended or whose inner solve restarts.
 __global__ void __launch_bounds__(128)
     batch_fin_schedule_kernel(const BatchSlot *__restrict__ slots, BatchSched sc) {
@@ -277,6 +286,14 @@ __global__ void __launch_bounds__((OpCfg<N1, EPB, MFMA>::THREADS))
       next = __builtin_amdgcn_readfirstlane(pre[k + 1]);
     }
     const BatchSlot &S = slots[__builtin_amdgcn_readfirstlane(sl[k])];
+    if constexpr (CLS != 3) {
+      // a solve that has stopped since the lists were built: skip its items
+      const CgState *st = CLS == 0 ? S.st : S.st_in;
+      if (__builtin_amdgcn_readfirstlane(st->done) != kRunning) {
+        w = next - 1;
+        continue;
+      }
+    }
     const int64_t e0 = (int64_t)(w - first) * EPB;
     if constexpr (CLS == 0) {
       batch_tile<N1, EPB, PrecF64, true, MFMA>(S.E, e0, S.D, S.G, S.p, S.w, S.r, S.minv, S.x,
@@ -312,7 +329,7 @@ __device__ __forceinline__ bool residual_item(const BatchSlot &S, int tile, doub
 // The end of an FP64 solve (x += alpha p), the correction of a mixed solve
 // (e += alpha p, x += ||r|| e) and the inner restart (r_in = r / ||r||,
 // e = p = 0 and the partials of its scalars); these phases are set by the
-// beta launch of the same iteration.
+// beta launches before.
 template <int N1, bool MIXED>
 __device__ __forceinline__ bool finish_item(const BatchSlot &S, int tile, double *sred) {
   if constexpr (!MIXED) {
@@ -510,10 +527,18 @@ __global__ void __launch_bounds__(kFinThreads)
         S.phase = kPhaseInnerDone;
       }
     }
-  } else if (phase == kPhaseOuterOp) {
-    outer_finish_step(S.st, S.part_rr, S.vtiles, sred);
-    if (threadIdx.x == 0) S.phase = S.st->done != kRunning ? kPhaseFinished : kPhaseRestart;
   }
+}
+
+// After the true residual of an outer step: the outer count, ||r|| and the
+// done flag of every solve in that phase.
+__global__ void __launch_bounds__(kFinThreads)
+    batch_outer_kernel(BatchSlot *__restrict__ slots) {
+  __shared__ double sred[2 * (kFinThreads / 64)];
+  BatchSlot &S = slots[blockIdx.x];
+  if (!S.active || S.mixed == 0 || S.phase != kPhaseOuterOp) return;
+  outer_finish_step(S.st, S.part_rr, S.vtiles, sred);
+  if (threadIdx.x == 0) S.phase = S.st->done != kRunning ? kPhaseFinished : kPhaseRestart;
 }
 
 __global__ void __launch_bounds__(kFinThreads)
@@ -595,12 +620,15 @@ void fill_grid(BatchGrids &g, int cus) {
     g.op[3][N][EPB] = resident_blocks(batch_op_kernel<N1, EPB, 3, MFMA>, T, cus, SEM_BATCH_GRID_MULT);
 }
 
+// Work-groups of a launch over a list of at most `bound` items.
+inline unsigned bounded_grid(int grid, int bound) { return (unsigned)(bound < grid ? (bound > 0 ? bound : 1) : grid); }
+
 template <int N1, int EPB, bool MFMA>
-bool launch_op(int cls, const BatchGrids &g, const BatchSlot *slots, const BatchSched &sc, int bin,
+bool launch_op(int cls, const BatchGrids &g, int bound, const BatchSlot *slots, const BatchSched &sc, int bin,
                hipStream_t s) {
   constexpr int N = N1 - 1;
   if (op_uses_mfma(cls, N) != MFMA) return false;
-  const dim3 grid(g.op[cls][N][EPB]), threads(OpCfg<N1, EPB, MFMA>::THREADS);
+  const dim3 grid(bounded_grid(g.op[cls][N][EPB], bound)), threads(OpCfg<N1, EPB, MFMA>::THREADS);
   if constexpr (op_uses_mfma(0, N) == MFMA)
     if (cls == 0) hipLaunchKernelGGL((batch_op_kernel<N1, EPB, 0, MFMA>), grid, threads, 0, s, slots, sc, bin);
   if constexpr (op_uses_mfma(1, N) == MFMA)
@@ -611,6 +639,94 @@ bool launch_op(int cls, const BatchGrids &g, const BatchSlot *slots, const Batch
     if (cls == 3) hipLaunchKernelGGL((batch_op_kernel<N1, EPB, 3, MFMA>), grid, threads, 0, s, slots, sc, bin);
   return true;
 }
+
+// Everything a batched step launches into one stream.
+struct BatchLaunch {
+  BatchSlot *slots;
+  int max_slots;
+  const BatchSched &sched;
+  const BatchTiles &tiles;
+  uint64_t bins;
+  const BatchBounds &bounds;
+  BatchStatus *status;
+  const BatchGrids &g;
+  hipStream_t s;
+
+  bool in_use(int cls, int N) const { return ((bins >> batch_bin(cls, N)) & 1u) != 0; }
+  bool f64() const { return ((bins >> kBatchBins) & 1u) != 0; }
+  bool mixed() const { return ((bins >> (kBatchBins + 1)) & 1u) != 0; }
+
+  // The operator launches of classes c0 .. c1; false: a tile that is not built.
+  bool operators(int c0, int c1) const {
+    for (int cls = c0; cls <= c1; ++cls)
+      for (int N = 1; N <= kBatchOrders; ++N) {
+        if (!in_use(cls, N)) continue;
+        const int bin = batch_bin(cls, N);
+        const int epb = tiles.epb[cls][N];
+        bool launched = false;
+#define LCASE_V(n_, epb_)                                                                \
+  if (!launched && N == n_ && epb == epb_)                                               \
+    launched = launch_op<n_ + 1, epb_, false>(cls, g, bounds.op[bin], slots, sched, bin, s);
+#define LCASE_M(n_, epb_)                                                                \
+  if (!launched && N == n_ && epb == epb_)                                               \
+    launched = launch_op<n_ + 1, epb_, true>(cls, g, bounds.op[bin], slots, sched, bin, s);
+        SEM_BATCH_TILES_VALU(LCASE_V)
+        SEM_BATCH_TILES_MFMA(LCASE_M)
+#undef LCASE_V
+#undef LCASE_M
+        if (!launched) return false;
+      }
+    return true;
+  }
+
+  void schedule() const {
+    hipLaunchKernelGGL(batch_schedule_kernel, dim3(1), dim3(kSchedThreads), 0, s, slots, sched, tiles);
+  }
+  bool iteration() const {
+    if (!operators(0, 2)) return false;
+    hipLaunchKernelGGL(batch_alpha_kernel, dim3(max_slots), dim3(kFinThreads), 0, s, slots);
+#define UCASE(n_)                                                                                        \
+  if (in_use(0, n_))                                                                                     \
+    hipLaunchKernelGGL((batch_upd_kernel<n_ + 1, false>),                                                \
+                       dim3(xcd_grid(bounded_grid(g.upd[0][n_], bounds.upd[0][n_]))),                    \
+                       dim3(BatchUpd<n_ + 1, false>::BLOCK), 0, s, slots, sched, batch_upd_list(0, n_)); \
+  if (in_use(1, n_) || in_use(2, n_))                                                                    \
+    hipLaunchKernelGGL((batch_upd_kernel<n_ + 1, true>),                                                 \
+                       dim3(xcd_grid(bounded_grid(g.upd[1][n_], bounds.upd[1][n_]))),                    \
+                       dim3(BatchUpd<n_ + 1, true>::BLOCK), 0, s, slots, sched, batch_upd_list(1, n_));
+    SEM_BATCH_ORDERS(UCASE)
+#undef UCASE
+    hipLaunchKernelGGL(batch_beta_kernel, dim3(max_slots), dim3(kFinThreads), 0, s, slots);
+    return true;
+  }
+
+  // The work of the phases that end an iteration (the last x += alpha p, the
+  // outer correction, the inner restart), then the phases themselves.
+  void finish(bool f, bool m) const {
+    hipLaunchKernelGGL(batch_fin_schedule_kernel, dim3(1), dim3(128), 0, s, slots, sched);
+    if (f)
+      hipLaunchKernelGGL((batch_fin_kernel<false>), dim3(g.fin[0]), dim3(kVecThreads), 0, s, slots, sched);
+    if (m)
+      hipLaunchKernelGGL((batch_fin_kernel<true>), dim3(g.fin[1]), dim3(kVecThreads), 0, s, slots, sched);
+    hipLaunchKernelGGL(batch_phase_kernel, dim3(max_slots), dim3(kFinThreads), 0, s, slots, status);
+  }
+
+  // Every solve that has stopped goes through the phases it owes: an FP64
+  // solve its last x += alpha p; a mixed one the outer correction, the true
+  // residual and the restart of its inner solve.  Then the lists are rebuilt.
+  bool phases() const {
+    finish(f64(), mixed());
+    if (mixed()) {
+      schedule();
+      if (!operators(3, 3)) return false;
+      hipLaunchKernelGGL(batch_resid_kernel, dim3(g.resid), dim3(kVecThreads), 0, s, slots, sched);
+      hipLaunchKernelGGL(batch_outer_kernel, dim3(max_slots), dim3(kFinThreads), 0, s, slots);
+      finish(false, true);
+    }
+    schedule();
+    return true;
+  }
+};
 
 }  // namespace
 
@@ -672,55 +788,20 @@ hipError_t batch_prepare() {
   return hipSuccess;
 }
 
-hipError_t launch_batch_iteration(BatchSlot *slots, int max_slots, const BatchSched &sched,
-                                  const BatchTiles &tiles, uint64_t bins, BatchStatus *status,
-                                  hipStream_t s) {
+hipError_t launch_batch_step(BatchSlot *slots, int max_slots, const BatchSched &sched, const BatchTiles &tiles,
+                             uint64_t bins, const BatchBounds &bounds, BatchStatus *status, int iters,
+                             hipStream_t s) {
   const BatchGrids *g = current_grids();
   if (!g) return hipErrorNotInitialized;
-  hipLaunchKernelGGL(batch_schedule_kernel, dim3(1), dim3(kSchedThreads), 0, s, slots, sched, tiles);
-  for (int cls = 0; cls < kBatchClasses; ++cls)
-    for (int N = 1; N <= kBatchOrders; ++N) {
-      const int bin = batch_bin(cls, N);
-      if (!((bins >> bin) & 1u)) continue;
-      const int epb = tiles.epb[cls][N];
-      bool launched = false;
-#define LCASE_V(n_, epb_)                                                         \
-  if (!launched && N == n_ && epb == epb_)                                        \
-    launched = launch_op<n_ + 1, epb_, false>(cls, *g, slots, sched, bin, s);
-#define LCASE_M(n_, epb_)                                                         \
-  if (!launched && N == n_ && epb == epb_)                                        \
-    launched = launch_op<n_ + 1, epb_, true>(cls, *g, slots, sched, bin, s);
-      SEM_BATCH_TILES_VALU(LCASE_V)
-      SEM_BATCH_TILES_MFMA(LCASE_M)
-#undef LCASE_V
-#undef LCASE_M
-      if (!launched) return hipErrorInvalidValue;
-    }
-  hipLaunchKernelGGL(batch_alpha_kernel, dim3(max_slots), dim3(kFinThreads), 0, s, slots);
-  const bool f64 = (bins >> kBatchBins) & 1u, mix = (bins >> (kBatchBins + 1)) & 1u;
-  auto in_use = [&](int cls, int N) { return ((bins >> batch_bin(cls, N)) & 1u) != 0; };
-#define UCASE(n_)                                                                              \
-  if (in_use(0, n_))                                                                           \
-    hipLaunchKernelGGL((batch_upd_kernel<n_ + 1, false>), dim3(g->upd[0][n_]),                 \
-                       dim3(BatchUpd<n_ + 1, false>::BLOCK), 0, s, slots, sched,              \
-                       batch_upd_list(0, n_));                                                 \
-  if (in_use(1, n_) || in_use(2, n_))                                                          \
-    hipLaunchKernelGGL((batch_upd_kernel<n_ + 1, true>), dim3(g->upd[1][n_]),                  \
-                       dim3(BatchUpd<n_ + 1, true>::BLOCK), 0, s, slots, sched,               \
-                       batch_upd_list(1, n_));
-  SEM_BATCH_ORDERS(UCASE)
-#undef UCASE
-  if (mix)
-    hipLaunchKernelGGL(batch_resid_kernel, dim3(g->resid), dim3(kVecThreads), 0, s, slots, sched);
-  hipLaunchKernelGGL(batch_beta_kernel, dim3(max_slots), dim3(kFinThreads), 0, s, slots);
-  hipLaunchKernelGGL(batch_fin_schedule_kernel, dim3(1), dim3(128), 0, s, slots, sched);
-  if (f64)
-    hipLaunchKernelGGL((batch_fin_kernel<false>), dim3(g->fin[0]), dim3(kVecThreads), 0, s, slots,
-                       sched);
-  if (mix)
-    hipLaunchKernelGGL((batch_fin_kernel<true>), dim3(g->fin[1]), dim3(kVecThreads), 0, s, slots,
-                       sched);
-  hipLaunchKernelGGL(batch_phase_kernel, dim3(max_slots), dim3(kFinThreads), 0, s, slots, status);
+  const BatchLaunch B{slots, max_slots, sched, tiles, bins, bounds, status, *g, s};
+  // solves that joined since the last step: a mixed one starts its inner solve
+  if (B.mixed()) B.finish(false, true);
+  B.schedule();
+  for (int it = 0; it < iters; ++it) {
+    if (!B.iteration()) return hipErrorInvalidValue;
+    if ((it + 1) % kBatchPhaseEvery == 0 || it + 1 == iters)
+      if (!B.phases()) return hipErrorInvalidValue;
+  }
   return hipGetLastError();
 }
 

@@ -20,13 +20,16 @@ bool batch_epb_supported(int cls, int N, int epb);
 // (queried once per process; call before graph capture).
 hipError_t batch_prepare();
 
-// One batched iteration over every active slot: the schedule, one operator
-// launch per bin set in `bins` (bit cls * 11 + N - 1), the per-solve scalar
-// launches and the streaming launches of the FP64 and mixed solves (bits
-// kBatchBins and kBatchBins + 1 of `bins`: which families are present).
-hipError_t launch_batch_iteration(BatchSlot *slots, int max_slots, const BatchSched &sched,
-                                  const BatchTiles &tiles, uint64_t bins, BatchStatus *status,
-                                  hipStream_t s);
+// `iters` batched iterations over every active slot.  An iteration is one
+// operator launch per bin of classes 0..2 set in `bins` (bit cls * 11 + N - 1),
+// the alpha steps, one update launch per order and family in use and the beta
+// steps; the phases advance after every kBatchPhaseEvery of them and after the
+// last (bits kBatchBins and kBatchBins + 1 of `bins`: FP64 and mixed solves
+// present).
+constexpr int kBatchPhaseEvery = 10;
+hipError_t launch_batch_step(BatchSlot *slots, int max_slots, const BatchSched &sched, const BatchTiles &tiles,
+                             uint64_t bins, const BatchBounds &bounds, BatchStatus *status, int iters,
+                             hipStream_t s);
 
 // ---------------------------------------------------------------- launchers
 // All return the hipError_t of the launch (hipGetLastError after it).

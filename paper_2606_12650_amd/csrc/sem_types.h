@@ -336,4 +336,13 @@ struct BatchTiles {
   int epb[kBatchClasses][kBatchOrders + 1];
 };
 
+// Upper bounds of the work in a batch's lists, from its occupied slots: the
+// items of each operator bin and of each update list.  A launch takes no more
+// work-groups than its bound.  Rounded up to powers of two, so that a captured
+// step outlives most joins and leaves.
+struct BatchBounds {
+  int op[kBatchBins];
+  int upd[2][kBatchOrders + 1];
+};
+
 }  // namespace semk
