@@ -444,12 +444,7 @@ int sem_setup(const sem_mesh_desc *desc, void *dev_ws, size_t ws_bytes, void *st
     return bail(hip_fail(e, "sem_setup: upload D"));
   if ((e = hipMemcpyAsync(c->nodes, nodes.data(), nodes.size() * sizeof(double), hipMemcpyHostToDevice, s)) != hipSuccess)
     return bail(hip_fail(e, "sem_setup: upload nodes"));
-  // element-local diagonal into r (scratch), then Minv = 1 / (sum of copies)
-  if ((e = semk::launch_setup_geom(c->box, desc->deform_amp, c->D, c->nodes, c->G, c->r, s)) != hipSuccess)
-    return bail(hip_fail(e, "sem_setup: geometry kernel"));
-  if ((e = semk::launch_gather(c->box, c->r, c->minv, semk::kGatherInverse, s)) != hipSuccess)
-    return bail(hip_fail(e, "sem_setup: diagonal gather-scatter"));
-  // low-precision copy: D rounded on the host, G and Minv rounded on the GPU
+  // low-precision copy: D rounded on the host, G and Minv as they are formed
   std::vector<float> Dlo(D.size());
   if (lowp) {
     for (size_t q = 0; q < D.size(); ++q) {
@@ -458,12 +453,13 @@ int sem_setup(const sem_mesh_desc *desc, void *dev_ws, size_t ws_bytes, void *st
     }
     if ((e = hipMemcpyAsync(c->Dlo, Dlo.data(), Dlo.size() * sizeof(float), hipMemcpyHostToDevice, s)) != hipSuccess)
       return bail(hip_fail(e, "sem_setup: upload rounded D"));
-    const int64_t L = c->box.L();
-    if ((e = semk::launch_convert_g(desc->lowprec, 6 * L, c->G, c->Glo, s)) != hipSuccess)
-      return bail(hip_fail(e, "sem_setup: round G"));
-    if ((e = semk::launch_convert_g(SEM_F32, L, c->minv, c->minv32, s)) != hipSuccess)
-      return bail(hip_fail(e, "sem_setup: round Minv"));
   }
+  // element-local diagonal into r (scratch), then Minv = 1 / (sum of copies)
+  if ((e = semk::launch_setup_geom(c->box, desc->deform_amp, c->D, c->nodes, c->G, c->r, desc->lowprec, c->Glo,
+                                   s)) != hipSuccess)
+    return bail(hip_fail(e, "sem_setup: geometry kernel"));
+  if ((e = semk::launch_gather(c->box, c->r, c->minv, semk::kGatherInverse, s, c->minv32)) != hipSuccess)
+    return bail(hip_fail(e, "sem_setup: diagonal gather-scatter"));
   if ((e = hipStreamSynchronize(s)) != hipSuccess) return bail(hip_fail(e, "sem_setup: synchronize"));
   *out = c;
   return SEM_OK;

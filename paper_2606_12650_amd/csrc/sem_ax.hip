@@ -15,19 +15,6 @@ namespace semk {
 
 namespace {
 
-// Rounded copy of G for a low-precision operator.
-template <class P>
-__global__ void __launch_bounds__(256)
-    convert_g_kernel(int64_t n, const double *__restrict__ src, typename P::TG *__restrict__ dst) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= n) return;
-  if constexpr (P::kBf16) {
-    dst[i] = bf16_bits((float)src[i]);
-  } else {
-    dst[i] = (typename P::TG)src[i];
-  }
-}
-
 template <int N1, class P>
 hipError_t ax_dispatch(const Box &b, const void *D, const void *G, void *u, void *w, const void *r,
                        const void *minv, void *x, CgState *cg, double *part, hipStream_t s,
@@ -83,12 +70,13 @@ hipError_t mfma_dispatch(const Box &b, const void *D, const void *G, void *u, vo
 
 template <int N1>
 hipError_t setup_dispatch(const Box &b, double amp, const double *D, const double *nodes,
-                          double *G, double *diag, hipStream_t s) {
+                          double *G, double *diag, int prec, void *Glo, hipStream_t s) {
   using C = AxCfg<N1>;
   const int64_t blocks = (b.E() + C::EPB - 1) / C::EPB;
   if (blocks == 0) return hipSuccess;
   hipLaunchKernelGGL((setup_geom_kernel<N1>), dim3((unsigned)blocks), dim3(C::THREADS), 0, s, b,
-                     amp, D, nodes, G, diag);
+                     amp, D, nodes, G, diag, prec == SEM_F32 ? (float *)Glo : nullptr,
+                     prec == SEM_BF16 ? (uint16_t *)Glo : nullptr);
   return hipGetLastError();
 }
 
@@ -151,26 +139,13 @@ hipError_t launch_ax_lowp(const Box &b, int prec, int impl, const float *D, cons
   return hipErrorInvalidValue;
 }
 
-hipError_t launch_convert_g(int prec, int64_t n, const double *src, void *dst, hipStream_t s) {
-  if (n == 0) return hipSuccess;
-  const unsigned blocks = (unsigned)((n + 255) / 256);
-  if (prec == SEM_F32)
-    hipLaunchKernelGGL(convert_g_kernel<PrecF32>, dim3(blocks), dim3(256), 0, s, n, src, (float *)dst);
-  else if (prec == SEM_BF16)
-    hipLaunchKernelGGL(convert_g_kernel<PrecBF16>, dim3(blocks), dim3(256), 0, s, n, src,
-                       (uint16_t *)dst);
-  else
-    return hipErrorInvalidValue;
-  return hipGetLastError();
-}
-
 hipError_t launch_setup_geom(const Box &b, double amp, const double *D, const double *nodes,
-                             double *G, double *diag, hipStream_t s) {
+                             double *G, double *diag, int prec, void *Glo, hipStream_t s) {
   if (rtc_order(b.N)) return rtc_setup_geom(b, amp, D, nodes, G, diag, s);
   switch (b.N) {
 #define CASE(n) \
   case n:       \
-    return setup_dispatch<n + 1>(b, amp, D, nodes, G, diag, s);
+    return setup_dispatch<n + 1>(b, amp, D, nodes, G, diag, prec, Glo, s);
     SEM_FOR_EACH_ORDER(CASE)
 #undef CASE
     default:

@@ -34,9 +34,10 @@ hipError_t launch_batch_step(BatchSlot *slots, int max_slots, const BatchSched &
 // ---------------------------------------------------------------- launchers
 // All return the hipError_t of the launch (hipGetLastError after it).
 
-// G (E x 6 x np) and the element-local Jacobi diagonal (L) of box b.
+// G (E x 6 x np) and the element-local Jacobi diagonal (L) of box b; Glo (may
+// be null): G rounded to prec, SEM_F32 or SEM_BF16, as well.
 hipError_t launch_setup_geom(const Box &b, double amp, const double *D, const double *nodes,
-                             double *G, double *diag_local, hipStream_t s);
+                             double *G, double *diag_local, int prec, void *Glo, hipStream_t s);
 // Inverse multiplicity c as an L-vector.
 hipError_t launch_fill_c(const Box &b, double *c, hipStream_t s);
 
@@ -67,11 +68,10 @@ hipError_t launch_ax_f64(const Box &b, int impl, const double *D, const double *
 hipError_t launch_ax_lowp(const Box &b, int prec, int impl, const float *D, const void *G, float *u,
                           float *w, const float *r, const float *minv, float *x, CgState *cg,
                           double *part, hipStream_t s, bool stream_w = false, const CgFold &fold = {});
-// dst[i] = src[i] rounded to float (SEM_F32) or to bfloat16 bits (SEM_BF16).
-hipError_t launch_convert_g(int prec, int64_t n, const double *src, void *dst, hipStream_t s);
-
 // out = the copies of every node of wl summed (GatherMode); wl != out.
-hipError_t launch_gather(const Box &b, const double *wl, double *out, int mode, hipStream_t s);
+// out32 (may be null, kGatherInverse only): out rounded to FP32 as well.
+hipError_t launch_gather(const Box &b, const double *wl, double *out, int mode, hipStream_t s,
+                         float *out32 = nullptr);
 hipError_t launch_gather_f32(const Box &b, const float *wl, float *out, int mode, hipStream_t s);
 
 // CG start: x = 0, r = mask o b, p = 0, partials of <r, Minv r>_c and

@@ -149,19 +149,29 @@ __global__ void __launch_bounds__(MfmaCfg<N1>::THREADS, (mfma_waves_per_simd<N1,
 
 // Metric setup: coordinates of the (deformed) box mesh, isoparametric
 // Jacobian by D along r, s, t, G = w_i w_j w_k det(J) J^-1 J^-T, then the
-// diagonal of the element operator.
+// diagonal of the element operator.  With a low-precision copy (G32 or G16,
+// else null) G is rounded into it as it is formed.
+//
+// One thread per (i, j) column: its three coordinates along t in registers, the
+// planes the r and s contractions read in LDS.  Nine contractions, the
+// cofactors and the diagonal come to about 250 FP64 operations a point at
+// N = 11 against the 56 bytes written, so the kernel is bound by the vector
+// units and LDS; every array index is a constant (unrolled), so that the
+// columns stay in registers.  A plane of coordinates is read by its own plane's
+// contractions only, so plane k of the three diagonal factors replaces it once
+// every thread is past it (one barrier per plane, no further LDS tile).
 template <int N1>
 __global__ void __launch_bounds__(AxCfg<N1>::THREADS)
     setup_geom_kernel(Box b, double amp, const double *__restrict__ Dg,
                       const double *__restrict__ nodes, double *__restrict__ G,
-                      double *__restrict__ diag) {
+                      double *__restrict__ diag, float *__restrict__ G32, uint16_t *__restrict__ G16) {
   using C = AxCfg<N1>;
   using T = AxTile<N1>;
   constexpr int NP = T::NP;
   constexpr int PL = N1 * N1;
-  constexpr int N = N1 - 1;
   __shared__ double sD[N1 * N1];
   __shared__ double sx[3][C::EPB * T::TILE];
+  __shared__ double sz[2][C::EPB * N1];  // Z0 and sin(2 pi Z0) of the element's planes
 
   const int tid = threadIdx.x;
   const int el = tid / PL;
@@ -173,9 +183,10 @@ __global__ void __launch_bounds__(AxCfg<N1>::THREADS)
   for (int t = tid; t < N1 * N1; t += C::THREADS) sD[t] = Dg[t];
 
   const int64_t ee = active ? e : 0;
-  const int ex = (int)(ee % b.nx);
-  const int ey = (int)((ee / b.nx) % b.ny);
-  const int ez = (int)(ee / ((int64_t)b.nx * b.ny));
+  const uint32_t eyz = b.fdx.div((uint32_t)ee);
+  const uint32_t ez = b.fdy.div(eyz);
+  const int ex = (int)((uint32_t)ee - eyz * (uint32_t)b.nx);
+  const int ey = (int)(eyz - ez * (uint32_t)b.ny);
   const double xi_i = nodes[i], xi_j = nodes[j];
   const double X0 = (ex + 0.5 * (xi_i + 1.0)) / b.nx;
   const double Y0 = (ey + 0.5 * (xi_j + 1.0)) / b.ny;
@@ -183,29 +194,47 @@ __global__ void __launch_bounds__(AxCfg<N1>::THREADS)
   double *SY = sx[1] + el * T::TILE;
   double *SZ = sx[2] + el * T::TILE;
   const double twopi = 2.0 * M_PI;
-  for (int k = 0; k < N1; ++k) {
-    const double Z0 = (ez + 0.5 * (nodes[k] + 1.0)) / b.nz;
-    double bump = 0.0;
-    if (amp != 0.0) bump = amp * sin(twopi * X0) * sin(twopi * Y0) * sin(twopi * Z0);
-    const int o = k * T::PLANE + j * T::P + i;
-    SX[o] = X0 + bump;
-    SY[o] = Y0 + bump;
-    SZ[o] = Z0 + bump;
+  if (ij < N1) {
+    const double Z0 = ((int)ez + 0.5 * (nodes[ij] + 1.0)) / b.nz;
+    sz[0][el * N1 + ij] = Z0;
+    sz[1][el * N1 + ij] = amp != 0.0 ? sin(twopi * Z0) : 0.0;
   }
+  __syncthreads();
+  double cx[N1], cy[N1], cz[N1];
+  const double bxy = amp != 0.0 ? amp * sin(twopi * X0) * sin(twopi * Y0) : 0.0;
+#pragma unroll
+  for (int k = 0; k < N1; ++k) {
+    const double bump = bxy * sz[1][el * N1 + k];
+    const int o = k * T::PLANE + j * T::P + i;
+    SX[o] = cx[k] = X0 + bump;
+    SY[o] = cy[k] = Y0 + bump;
+    SZ[o] = cz[k] = sz[0][el * N1 + k] + bump;
+  }
+  double Da[N1], Db[N1];
+#pragma unroll
+  for (int l = 0; l < N1; ++l) {
+    Da[l] = sD[i * N1 + l];
+    Db[l] = sD[j * N1 + l];
+  }
+  const double Dii = sD[i * N1 + i], Djj = sD[j * N1 + j];
   __syncthreads();
 
   const double wij = nodes[N1 + i] * nodes[N1 + j];
   const int64_t base = e * NP + ij;
-  double grr[N1], gss[N1], gtt[N1], grs[N1], grt[N1], gst[N1];
+  double cross[N1];            // the diagonal's part from the mixed factors
+  double g0 = 0, g1 = 0, g2 = 0;  // diagonal factors of the plane before
+#pragma unroll
   for (int k = 0; k < N1; ++k) {
     double J[3][3];
-    double *S[3] = {SX, SY, SZ};
+#pragma unroll
     for (int d = 0; d < 3; ++d) {
+      const double *S = d == 0 ? SX : (d == 1 ? SY : SZ);
       double a = 0.0, bb = 0.0, c = 0.0;
+#pragma unroll
       for (int l = 0; l < N1; ++l) {
-        a += sD[i * N1 + l] * S[d][k * T::PLANE + j * T::P + l];
-        bb += sD[j * N1 + l] * S[d][k * T::PLANE + l * T::P + i];
-        c += sD[k * N1 + l] * S[d][l * T::PLANE + j * T::P + i];
+        a += Da[l] * S[k * T::PLANE + j * T::P + l];
+        bb += Db[l] * S[k * T::PLANE + l * T::P + i];
+        c += Dg[k * N1 + l] * (d == 0 ? cx[l] : (d == 1 ? cy[l] : cz[l]));
       }
       J[d][0] = a;
       J[d][1] = bb;
@@ -228,54 +257,75 @@ __global__ void __launch_bounds__(AxCfg<N1>::THREADS)
     const double R1[3] = {c01 * inv, c11 * inv, c21 * inv};
     const double R2[3] = {c02 * inv, c12 * inv, c22 * inv};
     const double sc = wij * nodes[N1 + k] * det;
-    grr[k] = sc * (R0[0] * R0[0] + R0[1] * R0[1] + R0[2] * R0[2]);
-    grs[k] = sc * (R0[0] * R1[0] + R0[1] * R1[1] + R0[2] * R1[2]);
-    grt[k] = sc * (R0[0] * R2[0] + R0[1] * R2[1] + R0[2] * R2[2]);
-    gss[k] = sc * (R1[0] * R1[0] + R1[1] * R1[1] + R1[2] * R1[2]);
-    gst[k] = sc * (R1[0] * R2[0] + R1[1] * R2[1] + R1[2] * R2[2]);
-    gtt[k] = sc * (R2[0] * R2[0] + R2[1] * R2[1] + R2[2] * R2[2]);
+    const double g[6] = {sc * (R0[0] * R0[0] + R0[1] * R0[1] + R0[2] * R0[2]),
+                         sc * (R0[0] * R1[0] + R0[1] * R1[1] + R0[2] * R1[2]),
+                         sc * (R0[0] * R2[0] + R0[1] * R2[1] + R0[2] * R2[2]),
+                         sc * (R1[0] * R1[0] + R1[1] * R1[1] + R1[2] * R1[2]),
+                         sc * (R1[0] * R2[0] + R1[1] * R2[1] + R1[2] * R2[2]),
+                         sc * (R2[0] * R2[0] + R2[1] * R2[1] + R2[2] * R2[2])};
     if (active) {
-      double *Ge = G + e * 6 * NP + ij + k * PL;
-      Ge[0 * NP] = grr[k];
-      Ge[1 * NP] = grs[k];
-      Ge[2 * NP] = grt[k];
-      Ge[3 * NP] = gss[k];
-      Ge[4 * NP] = gst[k];
-      Ge[5 * NP] = gtt[k];
+      const int64_t at = e * 6 * NP + ij + k * PL;
+#pragma unroll
+      for (int q = 0; q < 6; ++q) G[at + q * NP] = g[q];
+      if (G32) {
+#pragma unroll
+        for (int q = 0; q < 6; ++q) G32[at + q * NP] = (float)g[q];
+      } else if (G16) {
+#pragma unroll
+        for (int q = 0; q < 6; ++q) G16[at + q * NP] = bf16_bits((float)g[q]);
+      }
     }
+    const double Dkk = Dg[k * N1 + k];
+    cross[k] = 2.0 * Dii * Djj * g[1] + 2.0 * Dii * Dkk * g[2] + 2.0 * Djj * Dkk * g[4];
+    if (k > 0) {  // every thread is past plane k - 1 (the barrier below)
+      const int o = (k - 1) * T::PLANE + j * T::P + i;
+      SX[o] = g0;
+      SY[o] = g1;
+      SZ[o] = g2;
+    }
+    g0 = g[0];
+    g1 = g[3];
+    g2 = g[5];
+    __syncthreads();
+  }
+  {
+    const int o = (N1 - 1) * T::PLANE + j * T::P + i;
+    SX[o] = g0;
+    SY[o] = g1;
+    SZ[o] = g2;
   }
   __syncthreads();
-  for (int k = 0; k < N1; ++k) {
-    const int o = k * T::PLANE + j * T::P + i;
-    SX[o] = grr[k];
-    SY[o] = gss[k];
-    SZ[o] = gtt[k];
+#pragma unroll
+  for (int l = 0; l < N1; ++l) {
+    const double a = sD[l * N1 + i], bb = sD[l * N1 + j];
+    Da[l] = a * a;
+    Db[l] = bb * bb;
   }
-  __syncthreads();
-  const double Dii = sD[i * N1 + i], Djj = sD[j * N1 + j];
+#pragma unroll
   for (int k = 0; k < N1; ++k) {
     double d = 0.0;
+#pragma unroll
     for (int l = 0; l < N1; ++l) {
-      const double a = sD[l * N1 + i], bb = sD[l * N1 + j], c = sD[l * N1 + k];
-      d += a * a * SX[k * T::PLANE + j * T::P + l];
-      d += bb * bb * SY[k * T::PLANE + l * T::P + i];
+      const double c = Dg[l * N1 + k];
+      d += Da[l] * SX[k * T::PLANE + j * T::P + l];
+      d += Db[l] * SY[k * T::PLANE + l * T::P + i];
       d += c * c * SZ[l * T::PLANE + j * T::P + i];
     }
-    const double Dkk = sD[k * N1 + k];
-    d += 2.0 * Dii * Djj * grs[k] + 2.0 * Dii * Dkk * grt[k] + 2.0 * Djj * Dkk * gst[k];
+    d += cross[k];
     if (active) diag[base + k * PL] = d;
   }
-  (void)N;
 }
 
 // ------------------------------------------------------------ gather-scatter
+// out32 (the Jacobi inverse only, may be null): the result rounded to FP32 too.
 // Linear tiles, with the index decode of the linear update tile (LinItems):
 // kLinGroup items at a time, every load of a group before its first sum
 // (masked FP64 gather at N = 9, 5083 elements: 23.6 -> 20.4 us against a
 // node-by-node decode).
 template <int N1, int MODE, typename T>
 __global__ void __launch_bounds__(kVecThreads)
-    gather_kernel(Box b, int64_t L, int64_t ntiles, const T *__restrict__ wl, T *__restrict__ out) {
+    gather_kernel(Box b, int64_t L, int64_t ntiles, const T *__restrict__ wl, T *__restrict__ out,
+                  float *__restrict__ out32) {
   const int64_t tile = chunk_tile(ntiles);
   if (tile >= ntiles) return;
   const LinItems<N1> P(b, tile, (int)threadIdx.x);
@@ -309,13 +359,19 @@ __global__ void __launch_bounds__(kVecThreads)
 #pragma unroll
   for (int u = 0; u < kVecItems; ++u)
     if (live[u]) out[P.raw0 + (uint32_t)(u * kVecThreads)] = res[u];
+  if (MODE == kGatherInverse && out32 != nullptr) {
+#pragma unroll
+    for (int u = 0; u < kVecItems; ++u)
+      if (live[u]) out32[P.raw0 + (uint32_t)(u * kVecThreads)] = (float)res[u];
+  }
 }
 
 // The same gather on element-column tiles (copies paired across faces, as
 // in the CG update).  V: the tile shape (upd_shape).
 template <int N1, int MODE, typename T, int V>
 __global__ void __launch_bounds__((UpdTile<N1, T, V>::BLOCK))
-    gather_col_kernel(Box b, int64_t ntiles, const T *__restrict__ wl, T *__restrict__ out) {
+    gather_col_kernel(Box b, int64_t ntiles, const T *__restrict__ wl, T *__restrict__ out,
+                      float *__restrict__ out32) {
   using U = UpdTile<N1, T, V>;
   __shared__ double sA[U::LDS];
   const int64_t tile = chunk_tile(ntiles);
@@ -333,6 +389,7 @@ __global__ void __launch_bounds__((UpdTile<N1, T, V>::BLOCK))
       else if (MODE == kGatherInverse)
         v = 1.0 / v;
       out[p.col0 + (int64_t)k * U::COLS] = (T)v;
+      if (MODE == kGatherInverse && out32 != nullptr) out32[p.col0 + (int64_t)k * U::COLS] = (float)v;
     }
   }
 }

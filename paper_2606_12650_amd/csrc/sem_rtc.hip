@@ -411,7 +411,9 @@ hipError_t rtc_setup_geom(const Box &b, double amp, const double *D, const doubl
                           double *diag, hipStream_t s) {
   const Shape sh = shape(b.N);
   Box bb = b;
-  void *args[] = {&bb, &amp, &D, &nodes, &G, &diag};
+  float *g32 = nullptr;
+  uint16_t *g16 = nullptr;
+  void *args[] = {&bb, &amp, &D, &nodes, &G, &diag, &g32, &g16};
   return launch(b.N, kRtcSetupGeom, dim3((unsigned)((b.E() + sh.setup_epb - 1) / sh.setup_epb)),
                 dim3(sh.setup_threads), s, args);
 }
@@ -434,7 +436,8 @@ hipError_t rtc_gather(const Box &b, const double *wl, double *out, int mode, hip
   if (k < 0) return hipErrorInvalidValue;
   Box bb = b;
   int64_t L = b.L(), nt = vec_num_blocks(L);
-  void *args[] = {&bb, &L, &nt, &wl, &out};
+  float *out32 = nullptr;
+  void *args[] = {&bb, &L, &nt, &wl, &out, &out32};
   return launch(b.N, k, dim3((unsigned)tile_grid(nt)), dim3(kVecThreads), s, args);
 }
 

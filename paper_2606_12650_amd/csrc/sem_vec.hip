@@ -287,30 +287,30 @@ inline dim3 xcd_vec_grid(int64_t n) { return dim3((unsigned)vec_grid_blocks(n));
 // The gather: the Jacobi set-up on the tiles the CG update of this order and
 // type uses, sem_ax on its own (kGatherShape).
 template <int N1, int MODE, typename T>
-void gather_launch(const Box &b, const T *wl, T *out, hipStream_t s) {
+void gather_launch(const Box &b, const T *wl, T *out, float *out32, hipStream_t s) {
   constexpr int V = MODE == kGatherInverse ? 0 : kGatherShape;
   if constexpr (UpdTile<N1, T, V>::LINEAR) {
     const int64_t L = b.L();
     hipLaunchKernelGGL((gather_kernel<N1, MODE, T>), dim3((unsigned)tile_grid(vec_num_blocks(L))),
-                       dim3(kVecThreads), 0, s, b, L, vec_num_blocks(L), wl, out);
+                       dim3(kVecThreads), 0, s, b, L, vec_num_blocks(L), wl, out, out32);
   } else {
     const bool f64 = sizeof(T) == 8;
     hipLaunchKernelGGL((gather_col_kernel<N1, MODE, T, V>), dim3((unsigned)upd_grid_blocks(b, f64, V)),
-                       dim3(UpdTile<N1, T, V>::BLOCK), 0, s, b, upd_num_tiles(b, f64, V), wl, out);
+                       dim3(UpdTile<N1, T, V>::BLOCK), 0, s, b, upd_num_tiles(b, f64, V), wl, out, out32);
   }
 }
 
 template <typename T>
-hipError_t gather_typed(const Box &b, const T *wl, T *out, int mode, hipStream_t s) {
+hipError_t gather_typed(const Box &b, const T *wl, T *out, int mode, float *out32, hipStream_t s) {
   if (b.L() == 0) return hipSuccess;
   if (mode != kGatherAssembled && mode != kGatherMasked && mode != kGatherInverse)
     return hipErrorInvalidValue;
   switch (b.N) {
 #define GCASE(n_)                                                                 \
   case n_:                                                                        \
-    if (mode == kGatherAssembled) gather_launch<n_ + 1, kGatherAssembled, T>(b, wl, out, s); \
-    else if (mode == kGatherMasked) gather_launch<n_ + 1, kGatherMasked, T>(b, wl, out, s);  \
-    else gather_launch<n_ + 1, kGatherInverse, T>(b, wl, out, s);                   \
+    if (mode == kGatherAssembled) gather_launch<n_ + 1, kGatherAssembled, T>(b, wl, out, out32, s); \
+    else if (mode == kGatherMasked) gather_launch<n_ + 1, kGatherMasked, T>(b, wl, out, out32, s);  \
+    else gather_launch<n_ + 1, kGatherInverse, T>(b, wl, out, out32, s);                   \
     break;
     GCASE(1) GCASE(2) GCASE(3) GCASE(4) GCASE(5) GCASE(6)
     GCASE(7) GCASE(8) GCASE(9) GCASE(10) GCASE(11) GCASE(12)
@@ -321,13 +321,13 @@ hipError_t gather_typed(const Box &b, const T *wl, T *out, int mode, hipStream_t
   return hipGetLastError();
 }
 
-hipError_t launch_gather(const Box &b, const double *wl, double *out, int mode, hipStream_t s) {
+hipError_t launch_gather(const Box &b, const double *wl, double *out, int mode, hipStream_t s, float *out32) {
   if (rtc_order(b.N)) return b.L() == 0 ? hipSuccess : rtc_gather(b, wl, out, mode, s);
-  return gather_typed<double>(b, wl, out, mode, s);
+  return gather_typed<double>(b, wl, out, mode, out32, s);
 }
 
 hipError_t launch_gather_f32(const Box &b, const float *wl, float *out, int mode, hipStream_t s) {
-  return gather_typed<float>(b, wl, out, mode, s);
+  return gather_typed<float>(b, wl, out, mode, nullptr, s);
 }
 
 hipError_t launch_cg_init(const Box &b, const double *bvec, double *x, double *r, double *p,
