@@ -50,7 +50,7 @@ size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 // precision block (Dlo .. state_in) exists only when desc.lowprec != SEM_F64.
 struct Layout {
   size_t D, nodes, G, minv, r, p, w, part_ax, part_rr, part_rz, state;
-  size_t Dlo, Glo, minv32, e, rin, pin, win, state_in;
+  size_t Dlo, Glo, minv32, e, zin, pin, win, state_in;
   size_t total;
 };
 
@@ -108,14 +108,14 @@ Layout layout_of(const sem_mesh_desc *d) {
   o.part_rr = take((size_t)semk::stream_partials(b) * sizeof(double));
   o.part_rz = take((size_t)semk::stream_partials(b) * sizeof(double));
   o.state = take(semk::kCgStates * sizeof(CgState));
-  o.Dlo = o.Glo = o.minv32 = o.e = o.rin = o.pin = o.win = o.state_in = 0;
+  o.Dlo = o.Glo = o.minv32 = o.e = o.zin = o.pin = o.win = o.state_in = 0;
   if (d->lowprec != SEM_F64) {
     const size_t gbytes = d->lowprec == SEM_BF16 ? 2 : 4;
     o.Dlo = take(n1 * n1 * sizeof(float));
     o.Glo = take(6 * L * gbytes);
     o.minv32 = take(L * sizeof(float));
     o.e = take(L * sizeof(float));
-    o.rin = take(L * sizeof(float));
+    o.zin = take(L * sizeof(float));
     o.pin = take(L * sizeof(float));
     o.win = take(L * sizeof(float));
     o.state_in = take(semk::kCgStates * sizeof(CgState));
@@ -206,7 +206,7 @@ struct sem_ctx {
   double *D, *nodes, *G, *minv, *r, *p, *w, *part_ax, *part_rr, *part_rz;
   CgState *st;
   // low-precision copy (null when desc.lowprec == SEM_F64)
-  float *Dlo, *minv32, *e, *rin, *pin, *win;
+  float *Dlo, *minv32, *e, *zin, *pin, *win;
   void *Glo;
   CgState *st_in;
   // partial counts: elements, streaming tiles, FP64 and FP32 update tiles
@@ -243,7 +243,7 @@ int enqueue_cg_iterations(sem_ctx *c, double *x, int iters, hipStream_t s) {
   semk::CgFold f;
   if (folded) f = semk::CgFold{c->part_rr, c->part_rz, (int)c->n_upd_blocks, c->part_ax, (int)c->n_ax_blocks};
   for (int it = 0; it < iters; ++it) {
-    SEM_HIP(semk::launch_ax_f64(b, c->op_impl[0], c->D, c->G, c->p, c->w, c->r, c->cg_minv, x, c->st, c->part_ax, s,
+    SEM_HIP(semk::launch_ax_f64(b, c->op_impl[0], c->D, c->G, c->p, c->w, c->r, x, c->st, c->part_ax, s,
                                 false, f));
     if (!folded) SEM_HIP(semk::launch_cg_alpha(c->st, c->part_ax, c->n_ax_blocks, s));
     SEM_HIP(semk::launch_cg_update(b, c->upd_var[0], c->r, c->w, c->cg_minv, c->st, c->part_rr, c->part_rz, s, f));
@@ -262,10 +262,10 @@ int enqueue_inner_iterations(sem_ctx *c, double *, int iters, hipStream_t s) {
   if (folded)
     f = semk::CgFold{c->part_rr, c->part_rz, (int)c->n_upd_blocks_in, c->part_ax, (int)c->n_ax_blocks};
   for (int it = 0; it < iters; ++it) {
-    SEM_HIP(semk::launch_ax_lowp(b, c->desc.lowprec, c->op_impl[1], c->Dlo, c->Glo, c->pin, c->win, c->rin,
-                                 c->minv32, c->e, c->st_in, c->part_ax, s, false, f));
+    SEM_HIP(semk::launch_ax_lowp(b, c->desc.lowprec, c->op_impl[1], c->Dlo, c->Glo, c->pin, c->win, c->zin, c->e,
+                                 c->st_in, c->part_ax, s, false, f));
     if (!folded) SEM_HIP(semk::launch_cg_alpha(c->st_in, c->part_ax, c->n_ax_blocks, s));
-    SEM_HIP(semk::launch_cg_update_f32(b, c->upd_var[1], c->rin, c->win, c->minv32, c->st_in, c->part_rr,
+    SEM_HIP(semk::launch_cg_update_f32(b, c->upd_var[1], c->zin, c->win, c->minv32, c->st_in, c->part_rr,
                                        c->part_rz, s, f));
     if (!folded) SEM_HIP(semk::launch_cg_beta(c->st_in, c->part_rr, c->part_rz, c->n_upd_blocks_in, s));
   }
@@ -424,7 +424,7 @@ int sem_setup(const sem_mesh_desc *desc, void *dev_ws, size_t ws_bytes, void *st
   c->Glo = lowp ? (void *)(c->ws + lay.Glo) : nullptr;
   c->minv32 = lowp ? (float *)(c->ws + lay.minv32) : nullptr;
   c->e = lowp ? (float *)(c->ws + lay.e) : nullptr;
-  c->rin = lowp ? (float *)(c->ws + lay.rin) : nullptr;
+  c->zin = lowp ? (float *)(c->ws + lay.zin) : nullptr;
   c->pin = lowp ? (float *)(c->ws + lay.pin) : nullptr;
   c->win = lowp ? (float *)(c->ws + lay.win) : nullptr;
   c->st_in = lowp ? (CgState *)(c->ws + lay.state_in) : nullptr;
@@ -485,12 +485,12 @@ int sem_ax(sem_ctx *ctx, const double *u, double *w, int mode, void *stream) {
   hipStream_t s = (hipStream_t)stream;
   if (mode == SEM_AX_LOCAL) {  // the result goes to the caller: streamed stores
     SEM_HIP(semk::launch_ax_f64(ctx->box, ctx->op_impl[0], ctx->D, ctx->G, const_cast<double *>(u), w, nullptr,
-                                nullptr, nullptr, nullptr, nullptr, s, true));
+                                nullptr, nullptr, nullptr, s, true));
     return SEM_OK;
   }
   // element-local result into the workspace, then the gather-scatter pull
   SEM_HIP(semk::launch_ax_f64(ctx->box, ctx->op_impl[0], ctx->D, ctx->G, const_cast<double *>(u), ctx->w, nullptr,
-                              nullptr, nullptr, nullptr, nullptr, s));
+                              nullptr, nullptr, nullptr, s));
   SEM_HIP(semk::launch_gather(ctx->box, ctx->w, w,
                               mode == SEM_AX_MASKED ? semk::kGatherMasked : semk::kGatherAssembled, s));
   return SEM_OK;
@@ -523,8 +523,9 @@ int sem_cg(sem_ctx *ctx, const double *b, double *x, const sem_cg_opts *opts, se
   h.max_iter = opts->mixed ? (opts->max_iter > 0 ? opts->max_iter : 50) : max_iter;
   h.rtol2 = opts->fixed_iter > 0 ? -1.0 : opts->rtol * opts->rtol;
   SEM_HIP(hipMemcpyAsync(ctx->st, &h, sizeof(CgState), hipMemcpyHostToDevice, s));
-  SEM_HIP(semk::launch_cg_init(ctx->box, b, x, ctx->r, ctx->p, ctx->cg_minv, ctx->st, ctx->part_rz,
-                               ctx->part_rr, s));
+  // FP64 CG: ctx->r holds z = Minv r; mixed: the outer residual itself
+  SEM_HIP(semk::launch_cg_init(ctx->box, b, x, ctx->r, ctx->p, opts->mixed ? nullptr : ctx->cg_minv, ctx->st,
+                               ctx->part_rz, ctx->part_rr, s));
   int status = SEM_OK;
   if (!opts->mixed) {
     if (every > max_iter) every = max_iter;
@@ -548,7 +549,7 @@ int sem_cg(sem_ctx *ctx, const double *b, double *x, const sem_cg_opts *opts, se
     SEM_HIP(hipMemcpyAsync(&h, ctx->st, sizeof(CgState), hipMemcpyDeviceToHost, s));
     SEM_HIP(hipStreamSynchronize(s));
     while (h.done == semk::kRunning) {
-      SEM_HIP(semk::launch_inner_start(bx, ctx->r, ctx->st, ctx->st_in, eta * eta, inner_max, ctx->rin,
+      SEM_HIP(semk::launch_inner_start(bx, ctx->r, ctx->st, ctx->st_in, eta * eta, inner_max, ctx->zin,
                                        ctx->e, ctx->pin, ctx->minv32, ctx->part_rz, ctx->part_rr, s));
       CgState &hi = ctx->host_inner;
       int rc = run_until_done(ctx, 1, enqueue_inner_iterations, nullptr, ctx->st_in, &hi, every,
@@ -556,7 +557,7 @@ int sem_cg(sem_ctx *ctx, const double *b, double *x, const sem_cg_opts *opts, se
       if (rc != SEM_OK) return rc;
       inner_total += hi.iter;
       SEM_HIP(semk::launch_outer_correct(bx, x, ctx->e, ctx->pin, ctx->st_in, ctx->st, s));
-      SEM_HIP(semk::launch_ax_f64(bx, ctx->op_impl[0], ctx->D, ctx->G, x, ctx->w, nullptr, nullptr, nullptr, nullptr,
+      SEM_HIP(semk::launch_ax_f64(bx, ctx->op_impl[0], ctx->D, ctx->G, x, ctx->w, nullptr, nullptr, nullptr,
                                   nullptr, s));
       SEM_HIP(semk::launch_outer_step(bx, b, ctx->w, ctx->r, ctx->st, ctx->part_rr, s));
       SEM_HIP(hipMemcpyAsync(&h, ctx->st, sizeof(CgState), hipMemcpyDeviceToHost, s));
@@ -589,7 +590,7 @@ int sem_ax_lowp(sem_ctx *ctx, const float *u, float *w, int mode, void *stream) 
   hipStream_t s = (hipStream_t)stream;
   float *dst = mode == SEM_AX_LOCAL ? w : ctx->win;
   SEM_HIP(semk::launch_ax_lowp(ctx->box, ctx->desc.lowprec, ctx->op_impl[1], ctx->Dlo,
-                               ctx->Glo, const_cast<float *>(u), dst, nullptr, nullptr, nullptr, nullptr,
+                               ctx->Glo, const_cast<float *>(u), dst, nullptr, nullptr, nullptr,
                                nullptr, s, mode == SEM_AX_LOCAL));
   if (mode != SEM_AX_LOCAL)
     SEM_HIP(semk::launch_gather_f32(ctx->box, ctx->win, w,
@@ -963,7 +964,7 @@ int sem_batch_add(sem_batch *B, sem_ctx *ctx, const double *b, double *x, const 
                            : (opts->max_iter > 0 ? opts->max_iter : 20000);
   h.rtol2 = opts->rtol * opts->rtol;
   SEM_HIP(hipMemcpyAsync(ctx->st, &h, sizeof(CgState), hipMemcpyHostToDevice, s));
-  SEM_HIP(semk::launch_cg_init(bx, b, x, ctx->r, ctx->p, ctx->minv, ctx->st, ctx->part_rz,
+  SEM_HIP(semk::launch_cg_init(bx, b, x, ctx->r, ctx->p, opts->mixed ? nullptr : ctx->minv, ctx->st, ctx->part_rz,
                                ctx->part_rr, s));
   SEM_HIP(hipMemcpyAsync(&h, ctx->st, sizeof(CgState), hipMemcpyDeviceToHost, s));
   SEM_HIP(hipStreamSynchronize(s));
@@ -995,7 +996,7 @@ int sem_batch_add(sem_batch *B, sem_ctx *ctx, const double *b, double *x, const 
   S.Glo = ctx->Glo;
   S.minv32 = ctx->minv32;
   S.e = ctx->e;
-  S.rin = ctx->rin;
+  S.zin = ctx->zin;
   S.pin = ctx->pin;
   S.win = ctx->win;
   S.st = ctx->st;

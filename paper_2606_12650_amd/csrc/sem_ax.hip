@@ -16,8 +16,7 @@ namespace semk {
 namespace {
 
 template <int N1, class P>
-hipError_t ax_dispatch(const Box &b, const void *D, const void *G, void *u, void *w, const void *r,
-                       const void *minv, void *x, CgState *cg, double *part, hipStream_t s,
+hipError_t ax_dispatch(const Box &b, const void *D, const void *G, void *u, void *w, const void *z, void *x, CgState *cg, double *part, hipStream_t s,
                        const CgFold &fold) {
   using C = OpCfg<N1>;
   using TV = typename P::TV;
@@ -27,22 +26,19 @@ hipError_t ax_dispatch(const Box &b, const void *D, const void *G, void *u, void
   if (blocks == 0) return hipSuccess;
   if (cg && fold.n_upd > 0)
     hipLaunchKernelGGL((ax_fold_kernel<N1, P>), dim3((unsigned)blocks), dim3(C::THREADS), 0, s, b.E(),
-                       (const TC *)D, (const TG *)G, (TV *)u, (TV *)w, (const TV *)r, (const TV *)minv,
+                       (const TC *)D, (const TG *)G, (TV *)u, (TV *)w, (const TV *)z,
                        (TV *)x, cg, part, fold.part_rr, fold.part_rz, fold.n_upd);
   else if (cg)
     hipLaunchKernelGGL((ax_kernel<N1, P, true>), dim3((unsigned)blocks), dim3(C::THREADS), 0, s,
-                       b.E(), (const TC *)D, (const TG *)G, (TV *)u, (TV *)w, (const TV *)r,
-                       (const TV *)minv, (TV *)x, cg, part);
+                       b.E(), (const TC *)D, (const TG *)G, (TV *)u, (TV *)w, (const TV *)z, (TV *)x, cg, part);
   else
     hipLaunchKernelGGL((ax_kernel<N1, P, false>), dim3((unsigned)blocks), dim3(C::THREADS), 0, s,
-                       b.E(), (const TC *)D, (const TG *)G, (TV *)u, (TV *)w, (const TV *)r,
-                       (const TV *)minv, (TV *)x, cg, part);
+                       b.E(), (const TC *)D, (const TG *)G, (TV *)u, (TV *)w, (const TV *)z, (TV *)x, cg, part);
   return hipGetLastError();
 }
 
 template <int N1, class P>
-hipError_t mfma_dispatch(const Box &b, const void *D, const void *G, void *u, void *w, const void *r,
-                         const void *minv, void *x, CgState *cg, double *part, hipStream_t s,
+hipError_t mfma_dispatch(const Box &b, const void *D, const void *G, void *u, void *w, const void *z, void *x, CgState *cg, double *part, hipStream_t s,
                          bool stream_w, const CgFold &fold) {
   using C = MfmaCfg<N1>;
   using TV = typename P::TV;
@@ -52,19 +48,17 @@ hipError_t mfma_dispatch(const Box &b, const void *D, const void *G, void *u, vo
   if (blocks == 0) return hipSuccess;
   if (cg && fold.n_upd > 0)
     hipLaunchKernelGGL((ax_mfma_fold_kernel<N1, P>), dim3((unsigned)blocks), dim3(C::THREADS), 0, s, b.E(),
-                       (const TC *)D, (const TG *)G, (TV *)u, (TV *)w, (const TV *)r, (const TV *)minv,
+                       (const TC *)D, (const TG *)G, (TV *)u, (TV *)w, (const TV *)z,
                        (TV *)x, cg, part, fold.part_rr, fold.part_rz, fold.n_upd);
   else if (cg)
     hipLaunchKernelGGL((ax_mfma_kernel<N1, P, true>), dim3((unsigned)blocks), dim3(C::THREADS), 0, s,
-                       b.E(), (const TC *)D, (const TG *)G, (TV *)u, (TV *)w, (const TV *)r,
-                       (const TV *)minv, (TV *)x, cg, part);
+                       b.E(), (const TC *)D, (const TG *)G, (TV *)u, (TV *)w, (const TV *)z, (TV *)x, cg, part);
   else if (stream_w)
     hipLaunchKernelGGL((ax_mfma_local_kernel<N1, P>), dim3((unsigned)blocks), dim3(C::THREADS), 0, s,
                        b.E(), (const TC *)D, (const TG *)G, (TV *)u, (TV *)w);
   else
     hipLaunchKernelGGL((ax_mfma_kernel<N1, P, false>), dim3((unsigned)blocks), dim3(C::THREADS), 0,
-                       s, b.E(), (const TC *)D, (const TG *)G, (TV *)u, (TV *)w, (const TV *)r,
-                       (const TV *)minv, (TV *)x, cg, part);
+                       s, b.E(), (const TC *)D, (const TG *)G, (TV *)u, (TV *)w, (const TV *)z, (TV *)x, cg, part);
   return hipGetLastError();
 }
 
@@ -106,14 +100,14 @@ int64_t ax_num_blocks(const Box &b) {
 // vector-unit one, by OpImpl.
 template <class P>
 hipError_t ax_launch(const Box &b, int cls, int impl, const void *D, const void *G, void *u, void *w,
-                     const void *r, const void *minv, void *x, CgState *cg, double *part,
+                     const void *z, void *x, CgState *cg, double *part,
                      hipStream_t s, bool stream_w, const CgFold &fold) {
   const bool mfma = impl == kImplMfma || (impl == kImplDefault && op_uses_mfma(cls, b.N));
   switch (b.N) {
 #define CASE(n)                                                                      \
   case n:                                                                            \
-    return mfma ? mfma_dispatch<n + 1, P>(b, D, G, u, w, r, minv, x, cg, part, s, stream_w, fold) \
-                : ax_dispatch<n + 1, P>(b, D, G, u, w, r, minv, x, cg, part, s, fold);
+    return mfma ? mfma_dispatch<n + 1, P>(b, D, G, u, w, z, x, cg, part, s, stream_w, fold) \
+                : ax_dispatch<n + 1, P>(b, D, G, u, w, z, x, cg, part, s, fold);
     SEM_FOR_EACH_ORDER(CASE)
 #undef CASE
     default:
@@ -122,20 +116,20 @@ hipError_t ax_launch(const Box &b, int cls, int impl, const void *D, const void 
 }
 
 hipError_t launch_ax_f64(const Box &b, int impl, const double *D, const double *G, double *u,
-                         double *w, const double *r, const double *minv, double *x, CgState *cg,
+                         double *w, const double *z, double *x, CgState *cg,
                          double *part, hipStream_t s, bool stream_w, const CgFold &fold) {
   if (rtc_order(b.N))  // run-time kernels: the matrix-core tile only
-    return impl == kImplValu ? hipErrorInvalidValue : rtc_ax_f64(b, D, G, u, w, r, minv, x, cg, part, s);
-  return ax_launch<PrecF64>(b, 0, impl, D, G, u, w, r, minv, x, cg, part, s, stream_w, fold);
+    return impl == kImplValu ? hipErrorInvalidValue : rtc_ax_f64(b, D, G, u, w, z, x, cg, part, s);
+  return ax_launch<PrecF64>(b, 0, impl, D, G, u, w, z, x, cg, part, s, stream_w, fold);
 }
 
 hipError_t launch_ax_lowp(const Box &b, int prec, int impl, const float *D, const void *G, float *u,
-                          float *w, const float *r, const float *minv, float *x, CgState *cg,
+                          float *w, const float *z, float *x, CgState *cg,
                           double *part, hipStream_t s, bool stream_w, const CgFold &fold) {
   if (prec == SEM_F32)
-    return ax_launch<PrecF32>(b, 1, impl, D, G, u, w, r, minv, x, cg, part, s, stream_w, fold);
+    return ax_launch<PrecF32>(b, 1, impl, D, G, u, w, z, x, cg, part, s, stream_w, fold);
   if (prec == SEM_BF16)
-    return ax_launch<PrecBF16>(b, 2, impl, D, G, u, w, r, minv, x, cg, part, s, stream_w, fold);
+    return ax_launch<PrecBF16>(b, 2, impl, D, G, u, w, z, x, cg, part, s, stream_w, fold);
   return hipErrorInvalidValue;
 }
 

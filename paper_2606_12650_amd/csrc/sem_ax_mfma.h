@@ -221,8 +221,7 @@ template <int N1, int EPB, class P, bool CG, bool OPQ = false, bool SW = false, 
 __device__ __forceinline__ void ax_tile_mfma(int64_t E, int64_t e0, const typename P::TC *__restrict__ Dg,
                                              const typename P::TG *__restrict__ G, typename P::TV *u,
                                              typename P::TV *__restrict__ w,
-                                             const typename P::TV *__restrict__ r,
-                                             const typename P::TV *__restrict__ minv,
+                                             const typename P::TV *__restrict__ z,
                                              typename P::TV *__restrict__ x, SC scalars,
                                              double *__restrict__ part_el,
                                              typename P::TC *sD, typename P::TC *s1,
@@ -268,14 +267,13 @@ __device__ __forceinline__ void ax_tile_mfma(int64_t E, int64_t e0, const typena
     const int pc = pt < NP ? pt : 0;
     off[m] = (pc / PL) * T::PLANE + ((pc % PL) / N1) * T::P + pc % N1;
   }
-  TV pv[PPT], xv[PPT], mv[PPT], rv[PPT];
+  TV pv[PPT], xv[PPT], zv[PPT];
 #pragma unroll
   for (int m = 0; m < PPT; ++m) {
     pv[m] = ld_once(u + idx[m]);
     if (CG) {
       xv[m] = ld_once(x + idx[m]);
-      mv[m] = minv_at(minv, r, idx[m]);
-      rv[m] = ld_once(r + idx[m]);
+      zv[m] = ld_once(z + idx[m]);
     }
   }
   // G with the prologue's loads, or in FP64 from N = 8 (LATE_G, mfma_late_g)
@@ -303,7 +301,8 @@ __device__ __forceinline__ void ax_tile_mfma(int64_t E, int64_t e0, const typena
     TV val = pv[m];
     if (CG) {
       const TV xn = xv[m] + (TV)alpha_d * pv[m];
-      val = mv[m] * rv[m] + (TV)beta_d * pv[m];
+      const TV bp = (TV)beta_d * pv[m];  // rounded by itself, then added
+      val = zv[m] + bp;
       if (okv[m]) {
         st_once(x + idx[m], xn);
         st_once(u + idx[m], val);

@@ -34,7 +34,7 @@ struct AxTile {
 // computed by the first N1*N1*EPB threads of the work-group (any others
 // only join the barriers).  Shared by the per-order kernels below and the
 // batched persistent kernel, so both produce the same bits.
-//   CG: prologue x += alpha p_old, p = Minv r + beta p_old (u is p), and the
+//   CG: prologue x += alpha p_old, p = z + beta p_old (u is p; z = Minv r), and the
 //   per-element sums of p.(A_L p) go to part_el[e] (summed in a fixed tree).
 // sD: N1*N1, s1/s2 (and s3 when AxTile<N1>::kTiles == 3): EPB *
 // AxTile<N1>::TILE values of TC each, sred: blockDim doubles, all in LDS.
@@ -42,8 +42,7 @@ template <int N1, int EPB, class P, bool CG, bool OPQ = false, class SC = GivenS
 __device__ __forceinline__ void ax_tile_col(int64_t E, int64_t e0, const typename P::TC *__restrict__ Dg,
                                         const typename P::TG *__restrict__ G, typename P::TV *u,
                                         typename P::TV *__restrict__ w,
-                                        const typename P::TV *__restrict__ r,
-                                        const typename P::TV *__restrict__ minv,
+                                        const typename P::TV *__restrict__ z,
                                         typename P::TV *__restrict__ x, SC scalars,
                                         double *__restrict__ part_el, typename P::TC *sD,
                                         typename P::TC *s1, typename P::TC *s2,
@@ -70,7 +69,7 @@ __device__ __forceinline__ void ax_tile_col(int64_t E, int64_t e0, const typenam
   const typename P::TG *Ge = G + (active ? e : 0) * 6 * NP + ij;
   TC uk[N1];  // the operand (p in CG), in the contraction type
   TC g[6][kPrefetchG ? N1 : 1];
-  TV pv[N1], xv[CG ? N1 : 1], mv[CG ? N1 : 1], rv[CG ? N1 : 1];
+  TV pv[N1], xv[CG ? N1 : 1], zv[CG ? N1 : 1];
   if (active) {
 #pragma unroll
     for (int k = 0; k < N1; ++k) {
@@ -78,8 +77,7 @@ __device__ __forceinline__ void ax_tile_col(int64_t E, int64_t e0, const typenam
       pv[k] = ld_once(u + idx);
       if constexpr (CG) {
         xv[k] = ld_once(x + idx);
-        mv[k] = minv_at(minv, r, idx);
-        rv[k] = ld_once(r + idx);
+        zv[k] = ld_once(z + idx);
       }
     }
     if constexpr (kPrefetchG) {
@@ -92,7 +90,7 @@ __device__ __forceinline__ void ax_tile_col(int64_t E, int64_t e0, const typenam
 #pragma unroll
     for (int k = 0; k < N1; ++k) {
       pv[k] = (TV)0;
-      if constexpr (CG) xv[k] = mv[k] = rv[k] = (TV)0;
+      if constexpr (CG) xv[k] = zv[k] = (TV)0;
       if constexpr (kPrefetchG) {
 #pragma unroll
         for (int q = 0; q < 6; ++q) g[q][k] = (TC)0;
@@ -105,7 +103,8 @@ __device__ __forceinline__ void ax_tile_col(int64_t E, int64_t e0, const typenam
     const TV beta = (TV)beta_d, alpha = (TV)alpha_d;
 #pragma unroll
     for (int k = 0; k < N1; ++k) {
-      const TV v = mv[k] * rv[k] + beta * pv[k];
+      const TV bp = beta * pv[k];  // rounded by itself, then added
+      const TV v = zv[k] + bp;
       if (active) {
         const int64_t idx = base + k * PL;
         st_once(x + idx, xv[k] + alpha * pv[k]);
@@ -232,8 +231,7 @@ template <int N1, int EPB, class P, bool CG, bool OPQ = false, class SC = GivenS
 __device__ __forceinline__ void ax_tile_split(int64_t E, int64_t e0, const typename P::TC *__restrict__ Dg,
                                               const typename P::TG *__restrict__ G, typename P::TV *u,
                                               typename P::TV *__restrict__ w,
-                                              const typename P::TV *__restrict__ r,
-                                              const typename P::TV *__restrict__ minv,
+                                              const typename P::TV *__restrict__ z,
                                               typename P::TV *__restrict__ x, SC scalars,
                                               double *__restrict__ part_el,
                                               typename P::TC *sD, typename P::TC *s1,
@@ -269,7 +267,7 @@ __device__ __forceinline__ void ax_tile_split(int64_t E, int64_t e0, const typen
   // predicated.  kc clamps the shorter second half of an odd order.
   TC uk[KH];  // this half of the operand (p in CG)
   int64_t idx[KH];
-  TV pv[KH], xv[KH], mv[KH], rv[KH];
+  TV pv[KH], xv[KH], zv[KH];
 #pragma unroll
   for (int kk = 0; kk < KH; ++kk) {
     const int kc = min(k0 + kk, N1 - 1);
@@ -277,8 +275,7 @@ __device__ __forceinline__ void ax_tile_split(int64_t E, int64_t e0, const typen
     pv[kk] = ld_once(u + idx[kk]);
     if (CG) {
       xv[kk] = ld_once(x + idx[kk]);
-      mv[kk] = minv_at(minv, r, idx[kk]);
-      rv[kk] = ld_once(r + idx[kk]);
+      zv[kk] = ld_once(z + idx[kk]);
     }
   }
   double alpha_d = 0.0, beta_d = 0.0;
@@ -291,7 +288,8 @@ __device__ __forceinline__ void ax_tile_split(int64_t E, int64_t e0, const typen
     TV v = pv[kk];
     if (CG) {
       const TV xn = xv[kk] + (TV)alpha_d * pv[kk];
-      v = mv[kk] * rv[kk] + (TV)beta_d * pv[kk];
+      const TV bp = (TV)beta_d * pv[kk];  // rounded by itself, then added
+      v = zv[kk] + bp;
       if (ok) {
         st_once(x + idx[kk], xn);
         st_once(u + idx[kk], v);
@@ -385,16 +383,15 @@ template <int N1, int EPB, class P, bool CG, bool OPQ = false, class SC = GivenS
 __device__ __forceinline__ void ax_tile(int64_t E, int64_t e0, const typename P::TC *__restrict__ Dg,
                                         const typename P::TG *__restrict__ G, typename P::TV *u,
                                         typename P::TV *__restrict__ w,
-                                        const typename P::TV *__restrict__ r,
-                                        const typename P::TV *__restrict__ minv,
+                                        const typename P::TV *__restrict__ z,
                                         typename P::TV *__restrict__ x, SC scalars,
                                         double *__restrict__ part_el, typename P::TC *sD,
                                         typename P::TC *s1, typename P::TC *s2,
                                         typename P::TC *s3, double *sred) {
   if constexpr (AxTile<N1>::kSplit)
-    ax_tile_split<N1, EPB, P, CG, OPQ>(E, e0, Dg, G, u, w, r, minv, x, scalars, part_el, sD, s1, s2, s3, sred);
+    ax_tile_split<N1, EPB, P, CG, OPQ>(E, e0, Dg, G, u, w, z, x, scalars, part_el, sD, s1, s2, s3, sred);
   else
-    ax_tile_col<N1, EPB, P, CG, OPQ>(E, e0, Dg, G, u, w, r, minv, x, scalars, part_el, sD, s1, s2, s3, sred);
+    ax_tile_col<N1, EPB, P, CG, OPQ>(E, e0, Dg, G, u, w, z, x, scalars, part_el, sD, s1, s2, s3, sred);
 }
 
 }  // namespace semk

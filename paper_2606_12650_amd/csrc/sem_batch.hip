@@ -242,15 +242,14 @@ __global__ void __launch_bounds__(128)
 template <int N1, int EPB, class P, bool CG, bool MFMA>
 __device__ __forceinline__ void batch_tile(int64_t E, int64_t e0, const typename P::TC *D,
                                            const typename P::TG *G, typename P::TV *u,
-                                           typename P::TV *w, const typename P::TV *r,
-                                           const typename P::TV *minv, typename P::TV *x,
+                                           typename P::TV *w, const typename P::TV *z, typename P::TV *x,
                                            const GivenScalars &sc, double *part,
                                            typename P::TC *sD, typename P::TC *s1,
                                            typename P::TC *s2, typename P::TC *s3, double *sred) {
   if constexpr (MFMA)
-    ax_tile_mfma<N1, EPB, P, CG, true>(E, e0, D, G, u, w, r, minv, x, sc, part, sD, s1, s2, s3, sred);
+    ax_tile_mfma<N1, EPB, P, CG, true>(E, e0, D, G, u, w, z, x, sc, part, sD, s1, s2, s3, sred);
   else
-    ax_tile<N1, EPB, P, CG, true>(E, e0, D, G, u, w, r, minv, x, sc, part, sD, s1, s2, s3, sred);
+    ax_tile<N1, EPB, P, CG, true>(E, e0, D, G, u, w, z, x, sc, part, sD, s1, s2, s3, sred);
 }
 
 template <int N1, int EPB, int CLS, bool MFMA>
@@ -296,16 +295,16 @@ __global__ void __launch_bounds__((OpCfg<N1, EPB, MFMA>::THREADS))
     }
     const int64_t e0 = (int64_t)(w - first) * EPB;
     if constexpr (CLS == 0) {
-      batch_tile<N1, EPB, PrecF64, true, MFMA>(S.E, e0, S.D, S.G, S.p, S.w, S.r, S.minv, S.x,
+      batch_tile<N1, EPB, PrecF64, true, MFMA>(S.E, e0, S.D, S.G, S.p, S.w, S.r, S.x,
                                                GivenScalars{S.st->alpha, S.st->beta}, S.part_el, sD, s1,
                                                s2, s3, sred);
     } else if constexpr (CLS == 3) {  // true-residual operator of a mixed solve's outer step
       batch_tile<N1, EPB, PrecF64, false, MFMA>(S.E, e0, S.D, S.G, S.x, S.w, nullptr, nullptr,
-                                                nullptr, GivenScalars{0.0, 0.0}, S.part_el, sD, s1, s2, s3,
+                                                GivenScalars{0.0, 0.0}, S.part_el, sD, s1, s2, s3,
                                                 sred);
     } else {
       batch_tile<N1, EPB, P, true, MFMA>(S.E, e0, S.Dlo, (const typename P::TG *)S.Glo, S.pin,
-                                         S.win, S.rin, S.minv32, S.e,
+                                         S.win, S.zin, S.e,
                                          GivenScalars{S.st_in->alpha, S.st_in->beta}, S.part_el, sD, s1, s2,
                                          s3, sred);
     }
@@ -348,7 +347,7 @@ __device__ __forceinline__ bool finish_item(const BatchSlot &S, int tile, double
                          sqrt(S.st->rnorm2));
     } else if (S.phase == kPhaseRestart) {
       const TileSums t = inner_start_tile<N1>(S.box, S.L, tile, S.r, 1.0 / sqrt(S.st->rnorm2),
-                                              S.rin, S.e, S.pin, S.minv32, sred);
+                                              S.zin, S.e, S.pin, S.minv32, sred);
       if (threadIdx.x == 0) {
         S.part_rz[tile] = t.a;
         S.part_rr[tile] = t.b;
@@ -434,7 +433,7 @@ __global__ void __launch_bounds__((BatchUpd<N1, MIXED>::BLOCK))
       prr = S.part_rr;
       prz = S.part_rz;
       if constexpr (MIXED) {
-        r = S.rin; wv = S.win; minv = S.minv32;
+        r = S.zin; wv = S.win; minv = S.minv32;
       } else {
         r = S.r; wv = S.w; minv = S.minv;
       }

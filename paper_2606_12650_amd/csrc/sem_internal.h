@@ -52,13 +52,13 @@ struct CgFold {
 };
 
 // w = A_L u.  With cg != null (a CG iteration) a prologue first finishes the
-// previous iteration, x += alpha p, then forms p <- Minv r + beta p (u is p,
+// previous iteration, x += alpha p, then forms p <- z + beta p (z = Minv r; u is p,
 // updated in place), and the per-element sums of p.w go to part (E of them).
 // impl: an OpImpl.  stream_w: w goes to the caller as it is (no gather reads
 // it next), so the matrix-core tile writes it with non-temporal stores (the
 // orders compiled at run time keep plain stores).
 hipError_t launch_ax_f64(const Box &b, int impl, const double *D, const double *G, double *u,
-                         double *w, const double *r, const double *minv, double *x, CgState *cg,
+                         double *w, const double *z, double *x, CgState *cg,
                          double *part, hipStream_t s, bool stream_w = false, const CgFold &fold = {});
 
 // Low-precision operator (prec SEM_F32 or SEM_BF16): FP32 vectors, G stored
@@ -66,7 +66,7 @@ hipError_t launch_ax_f64(const Box &b, int impl, const double *D, const double *
 // FP32 accumulation; the CG variant mirrors launch_ax_f64 (x is the inner
 // correction e).  impl: an OpImpl.
 hipError_t launch_ax_lowp(const Box &b, int prec, int impl, const float *D, const void *G, float *u,
-                          float *w, const float *r, const float *minv, float *x, CgState *cg,
+                          float *w, const float *z, float *x, CgState *cg,
                           double *part, hipStream_t s, bool stream_w = false, const CgFold &fold = {});
 // out = the copies of every node of wl summed (GatherMode); wl != out.
 // out32 (may be null, kGatherInverse only): out rounded to FP32 as well.
@@ -74,16 +74,16 @@ hipError_t launch_gather(const Box &b, const double *wl, double *out, int mode, 
                          float *out32 = nullptr);
 hipError_t launch_gather_f32(const Box &b, const float *wl, float *out, int mode, hipStream_t s);
 
-// CG start: x = 0, r = mask o b, p = 0, partials of <r, Minv r>_c and
+// CG start: x = 0, z = Minv r with r = mask o b, p = 0, partials of <r, z>_c and
 // ||b||_c^2; then a one-group launch sets rho, ||b||_c and the tolerance.
-hipError_t launch_cg_init(const Box &b, const double *bvec, double *x, double *r, double *p,
+hipError_t launch_cg_init(const Box &b, const double *bvec, double *x, double *z, double *p,
                           const double *minv, CgState *st, double *part_a, double *part_b,
                           hipStream_t s);
-// CG update with the gather of w fused in: r -= alpha mask o QQ^T w,
-// partials of ||r||_c^2 and <r, Minv r>_c (upd_num_tiles(b, f64, variant) of
+// CG update with the gather of w fused in: z -= alpha Minv o (mask o QQ^T w),
+// partials of ||r||_c^2 and <r, z>_c (upd_num_tiles(b, f64, variant) of
 // each).  Skipped when done.  variant: the update tile shape (upd_shape; the
 // orders compiled at run time have shape 0 only).
-hipError_t launch_cg_update(const Box &b, int variant, double *r, const double *w, const double *minv,
+hipError_t launch_cg_update(const Box &b, int variant, double *z, const double *w, const double *minv,
                             CgState *st, double *part_rr, double *part_rz, hipStream_t s,
                             const CgFold &fold = {});
 // One-group launches that finish the reductions and advance the scalars:
@@ -100,17 +100,17 @@ hipError_t launch_cg_beta_pending(CgState *st, const double *part_rr, const doub
 hipError_t launch_cg_finish(const Box &b, double *x, const double *p, const CgState *st,
                             hipStream_t s);
 // FP32 update for the inner solver of the inner-outer CG.
-hipError_t launch_cg_update_f32(const Box &b, int variant, float *r, const float *w, const float *minv,
+hipError_t launch_cg_update_f32(const Box &b, int variant, float *z, const float *w, const float *minv,
                                 CgState *st, double *part_rr, double *part_rz, hipStream_t s,
                                 const CgFold &fold = {});
 
-// Inner-outer CG steps.  inner_start: r_in = r / ||r||_c in FP32, e = p = 0,
+// Inner-outer CG steps.  inner_start: z_in = Minv r / ||r||_c in FP32, e = p = 0,
 // then the inner state: tolerance rtol2 = eta^2 (relative), iteration cap,
 // rho.  outer_correct: e += alpha_in p_in (if the inner solve's last update
 // ran), x += ||r||_c e.  outer_step (after w64 = A_L x): r = mask o (b -
 // QQ^T w64), ||r||_c^2, the outer count and the done flag.
 hipError_t launch_inner_start(const Box &b, const double *r64, CgState *outer, CgState *inner,
-                              double rtol2, int max_iter, float *rin, float *e, float *p,
+                              double rtol2, int max_iter, float *zin, float *e, float *p,
                               const float *minv32, double *part_a, double *part_b, hipStream_t s);
 hipError_t launch_outer_correct(const Box &b, double *x, float *e, const float *p,
                                 const CgState *inner, const CgState *outer, hipStream_t s);

@@ -43,8 +43,7 @@ template <int N1, class P, bool CG, class SC>
 __device__ __forceinline__ void ax_body(int64_t E, const typename P::TC *__restrict__ Dg,
                                         const typename P::TG *__restrict__ G, typename P::TV *u,
                                         typename P::TV *__restrict__ w,
-                                        const typename P::TV *__restrict__ r,
-                                        const typename P::TV *__restrict__ minv,
+                                        const typename P::TV *__restrict__ z,
                                         typename P::TV *__restrict__ x, const SC &scalars,
                                         double *__restrict__ part) {
   using C = OpCfg<N1>;
@@ -54,22 +53,22 @@ __device__ __forceinline__ void ax_body(int64_t E, const typename P::TC *__restr
   __shared__ TC s2[C::EPB * AxTile<N1>::TILE];
   __shared__ TC s3[AxTile<N1>::kTiles == 3 ? C::EPB * AxTile<N1>::TILE : 1];
   __shared__ double sred[CG ? C::THREADS : 1];
-  ax_tile<N1, C::EPB, P, CG, false, SC>(E, (int64_t)blockIdx.x * C::EPB, Dg, G, u, w, r, minv, x, scalars,
+  ax_tile<N1, C::EPB, P, CG, false, SC>(E, (int64_t)blockIdx.x * C::EPB, Dg, G, u, w, z, x, scalars,
                                         part, sD, s1, s2, s3, sred);
 }
 
 template <int N1, class P, bool CG>
 __global__ void __launch_bounds__(OpCfg<N1>::THREADS, OpCfg<N1>::MIN_WAVES)
     ax_kernel(int64_t E, const typename P::TC *__restrict__ Dg, const typename P::TG *__restrict__ G,
-              typename P::TV *u, typename P::TV *__restrict__ w, const typename P::TV *__restrict__ r,
-              const typename P::TV *__restrict__ minv, typename P::TV *__restrict__ x,
+              typename P::TV *u, typename P::TV *__restrict__ w, const typename P::TV *__restrict__ z,
+              typename P::TV *__restrict__ x,
               CgState *__restrict__ st, double *__restrict__ part) {
   GivenScalars sc{0.0, 0.0};
   if (CG) {
     if (st->done) return;  // uniform: converged solves skip all work
     sc = GivenScalars{st->alpha, st->beta};
   }
-  ax_body<N1, P, CG>(E, Dg, G, u, w, r, minv, x, sc, part);
+  ax_body<N1, P, CG>(E, Dg, G, u, w, z, x, sc, part);
 }
 
 // The CG operator of a folded iteration (cg_folded): the beta step of the
@@ -77,13 +76,13 @@ __global__ void __launch_bounds__(OpCfg<N1>::THREADS, OpCfg<N1>::MIN_WAVES)
 template <int N1, class P>
 __global__ void __launch_bounds__(OpCfg<N1>::THREADS, OpCfg<N1>::MIN_WAVES)
     ax_fold_kernel(int64_t E, const typename P::TC *__restrict__ Dg, const typename P::TG *__restrict__ G,
-                   typename P::TV *u, typename P::TV *__restrict__ w, const typename P::TV *__restrict__ r,
-                   const typename P::TV *__restrict__ minv, typename P::TV *__restrict__ x,
+                   typename P::TV *u, typename P::TV *__restrict__ w, const typename P::TV *__restrict__ z,
+                   typename P::TV *__restrict__ x,
                    CgState *__restrict__ st, double *__restrict__ part,
                    const double *__restrict__ part_rr, const double *__restrict__ part_rz, int n_upd) {
   __shared__ double sfold[2 * kFinGroup / 64];
   const FoldBeta<OpCfg<N1>::THREADS / 64> sc(st, part_rr, part_rz, n_upd, sfold);
-  ax_body<N1, P, true>(E, Dg, G, u, w, r, minv, x, sc, part);
+  ax_body<N1, P, true>(E, Dg, G, u, w, z, x, sc, part);
 }
 
 // The operator with the D contractions on the matrix cores (sem_ax_mfma.h):
@@ -92,8 +91,7 @@ template <int N1, class P, bool CG, bool SW, class SC>
 __device__ __forceinline__ void ax_mfma_body(int64_t E, const typename P::TC *__restrict__ Dg,
                                              const typename P::TG *__restrict__ G,
                                              typename P::TV *u, typename P::TV *__restrict__ w,
-                                             const typename P::TV *__restrict__ r,
-                                             const typename P::TV *__restrict__ minv,
+                                             const typename P::TV *__restrict__ z,
                                              typename P::TV *__restrict__ x, const SC &scalars,
                                              double *__restrict__ part) {
   using C = MfmaCfg<N1>;
@@ -103,7 +101,7 @@ __device__ __forceinline__ void ax_mfma_body(int64_t E, const typename P::TC *__
   __shared__ TC s2[C::EPB * AxTile<N1>::TILE];
   __shared__ TC s3[C::EPB * AxTile<N1>::TILE];
   __shared__ double sred[C::THREADS / 64];
-  ax_tile_mfma<N1, C::EPB, P, CG, false, SW, SC>(E, (int64_t)blockIdx.x * C::EPB, Dg, G, u, w, r, minv, x,
+  ax_tile_mfma<N1, C::EPB, P, CG, false, SW, SC>(E, (int64_t)blockIdx.x * C::EPB, Dg, G, u, w, z, x,
                                                  scalars, part, sD, s1, s2, s3, sred);
 }
 
@@ -111,15 +109,15 @@ template <int N1, class P, bool CG>
 __global__ void __launch_bounds__(MfmaCfg<N1>::THREADS, (mfma_waves_per_simd<N1, P, CG>()))
     ax_mfma_kernel(int64_t E, const typename P::TC *__restrict__ Dg,
                    const typename P::TG *__restrict__ G, typename P::TV *u,
-                   typename P::TV *__restrict__ w, const typename P::TV *__restrict__ r,
-                   const typename P::TV *__restrict__ minv, typename P::TV *__restrict__ x,
+                   typename P::TV *__restrict__ w, const typename P::TV *__restrict__ z,
+                   typename P::TV *__restrict__ x,
                    CgState *__restrict__ st, double *__restrict__ part) {
   GivenScalars sc{0.0, 0.0};
   if (CG) {
     if (st->done) return;  // uniform: converged solves skip all work
     sc = GivenScalars{st->alpha, st->beta};
   }
-  ax_mfma_body<N1, P, CG, false>(E, Dg, G, u, w, r, minv, x, sc, part);
+  ax_mfma_body<N1, P, CG, false>(E, Dg, G, u, w, z, x, sc, part);
 }
 
 // As ax_fold_kernel.
@@ -127,13 +125,13 @@ template <int N1, class P>
 __global__ void __launch_bounds__(MfmaCfg<N1>::THREADS, (mfma_waves_per_simd<N1, P, true>()))
     ax_mfma_fold_kernel(int64_t E, const typename P::TC *__restrict__ Dg,
                         const typename P::TG *__restrict__ G, typename P::TV *u,
-                        typename P::TV *__restrict__ w, const typename P::TV *__restrict__ r,
-                        const typename P::TV *__restrict__ minv, typename P::TV *__restrict__ x,
+                        typename P::TV *__restrict__ w, const typename P::TV *__restrict__ z,
+                        typename P::TV *__restrict__ x,
                         CgState *__restrict__ st, double *__restrict__ part,
                         const double *__restrict__ part_rr, const double *__restrict__ part_rz, int n_upd) {
   __shared__ double sfold[2 * kFinGroup / 64];
   const FoldBeta<MfmaCfg<N1>::THREADS / 64> sc(st, part_rr, part_rz, n_upd, sfold);
-  ax_mfma_body<N1, P, true, false>(E, Dg, G, u, w, r, minv, x, sc, part);
+  ax_mfma_body<N1, P, true, false>(E, Dg, G, u, w, z, x, sc, part);
 }
 
 // The element-local sem_ax, whose result goes to the caller as it is (no
@@ -144,7 +142,7 @@ __global__ void __launch_bounds__(MfmaCfg<N1>::THREADS, (mfma_waves_per_simd<N1,
     ax_mfma_local_kernel(int64_t E, const typename P::TC *__restrict__ Dg,
                          const typename P::TG *__restrict__ G, typename P::TV *u,
                          typename P::TV *__restrict__ w) {
-  ax_mfma_body<N1, P, false, true>(E, Dg, G, u, w, nullptr, nullptr, nullptr, GivenScalars{0.0, 0.0}, nullptr);
+  ax_mfma_body<N1, P, false, true>(E, Dg, G, u, w, nullptr, nullptr, GivenScalars{0.0, 0.0}, nullptr);
 }
 
 // Metric setup: coordinates of the (deformed) box mesh, isoparametric
@@ -432,7 +430,7 @@ __global__ void __launch_bounds__((UpdTile<N1, TV, V>::BLOCK))
 }
 
 // The update on the default tile with r written by non-temporal stores
-// (upd_streams_r), for vectors larger than the last-level cache.
+// (upd_streams_z), for vectors larger than the last-level cache.
 template <int N1, typename TV>
 __global__ void __launch_bounds__((UpdTile<N1, TV>::BLOCK))
     cg_update_stream_kernel(Box b, int64_t ntiles, TV *__restrict__ r, const TV *__restrict__ w,

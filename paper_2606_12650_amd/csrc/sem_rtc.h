@@ -35,7 +35,7 @@ hipError_t rtc_build(int N, const char *arch, size_t *code_bytes, std::string *w
 hipError_t rtc_setup_geom(const Box &b, double amp, const double *D, const double *nodes, double *G,
                           double *diag, hipStream_t s);
 hipError_t rtc_ax_f64(const Box &b, const double *D, const double *G, double *u, double *w,
-                      const double *r, const double *minv, double *x, CgState *cg, double *part,
+                      const double *z, double *x, CgState *cg, double *part,
                       hipStream_t s);
 hipError_t rtc_gather(const Box &b, const double *wl, double *out, int mode, hipStream_t s);
 hipError_t rtc_cg_init(const Box &b, const double *bvec, double *x, double *r, double *p,

@@ -419,11 +419,11 @@ hipError_t rtc_setup_geom(const Box &b, double amp, const double *D, const doubl
 }
 
 hipError_t rtc_ax_f64(const Box &b, const double *D, const double *G, double *u, double *w,
-                      const double *r, const double *minv, double *x, CgState *cg, double *part,
+                      const double *z, double *x, CgState *cg, double *part,
                       hipStream_t s) {
   const Shape sh = shape(b.N);
   int64_t E = b.E();
-  void *args[] = {&E, &D, &G, &u, &w, &r, &minv, &x, &cg, &part};
+  void *args[] = {&E, &D, &G, &u, &w, &z, &x, &cg, &part};
   return launch(b.N, cg ? kRtcAxCg : kRtcAx, dim3((unsigned)((E + sh.ax_epb - 1) / sh.ax_epb)),
                 dim3(sh.ax_threads), s, args);
 }

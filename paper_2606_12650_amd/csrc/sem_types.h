@@ -132,7 +132,7 @@ inline int64_t tile_grid(int64_t ntiles) {
   return m * ((ntiles + m - 1) / m);
 }
 
-// Tiles of the CG update (the gather-scatter pulled into r -= alpha w) are
+// Tiles of the CG update (the gather-scatter pulled into z -= alpha Minv w) are
 // element-aligned: upd_ept consecutive elements with upd_ks threads per
 // (i, j) column over all planes.  Up to order 7 a tile fills 256 threads; at
 // order 8 it holds two FP64 elements or one FP32 element with three threads
@@ -223,7 +223,7 @@ inline int64_t upd_grid_blocks(const Box &b, bool f64, int v = 0) { return tile_
 // update has yet to read (FP64 N = 11, 453 MB a vector: 369 -> 350 us); a
 // vector that fits is wanted there by the next operator launch (N = 7, 134 MB:
 // with non-temporal stores the operator went from 257 to 270 us).
-inline bool upd_streams_r(const Box &b, bool f64) { return b.L() * (f64 ? 8 : 4) > (int64_t)256 << 20; }
+inline bool upd_streams_z(const Box &b, bool f64) { return b.L() * (f64 ? 8 : 4) > (int64_t)256 << 20; }
 // Partials a solve's streaming reductions need room for (every candidate
 // update tile of both vector types).
 inline int64_t stream_partials(const Box &b) {
@@ -284,7 +284,7 @@ struct BatchSlot {
   double *minv, *r, *p, *w, *x;
   const float *Dlo;
   const void *Glo;
-  float *minv32, *e, *rin, *pin, *win;
+  float *minv32, *e, *zin, *pin, *win;
   CgState *st, *st_in;
   double *part_el, *part_rr, *part_rz;
 };

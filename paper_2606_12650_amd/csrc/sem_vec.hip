@@ -78,7 +78,7 @@ __global__ void __launch_bounds__(kVecThreads)
 template <int N1>
 __global__ void __launch_bounds__(kVecThreads)
     inner_start_kernel(Box b, int64_t L, int64_t ntiles, const double *__restrict__ r64,
-                       const CgState *__restrict__ outer, float *__restrict__ rin,
+                       const CgState *__restrict__ outer, float *__restrict__ zin,
                        float *__restrict__ e, float *__restrict__ p,
                        const float *__restrict__ minv32, double *__restrict__ part_rz,
                        double *__restrict__ part_rr) {
@@ -86,7 +86,7 @@ __global__ void __launch_bounds__(kVecThreads)
   const double inv_s = 1.0 / sqrt(outer->rnorm2);
   const int64_t tile = xcd_tile(ntiles);
   TileSums t{0.0, 0.0};
-  if (tile < ntiles) t = inner_start_tile<N1>(b, L, tile, r64, inv_s, rin, e, p, minv32, sred);
+  if (tile < ntiles) t = inner_start_tile<N1>(b, L, tile, r64, inv_s, zin, e, p, minv32, sred);
   if (threadIdx.x == 0) {
     part_rz[tile] = t.a;
     part_rr[tile] = t.b;
@@ -211,7 +211,7 @@ hipError_t update_launch(const Box &b, TV *r, const TV *w, const TV *minv, CgSta
                            part_rr, part_rz, fold.part_pap, fold.n_op);
       else
         return hipErrorInvalidValue;
-    } else if (V == 0 && upd_streams_r(b, f64)) {
+    } else if (V == 0 && upd_streams_z(b, f64)) {
       hipLaunchKernelGGL((cg_update_stream_kernel<N1, TV>), dim3((unsigned)upd_grid_blocks(b, f64)),
                          dim3(UpdTile<N1, TV>::BLOCK), 0, s, b, upd_num_tiles(b, f64), r, w, minv, st, part_rr,
                          part_rz);
@@ -390,12 +390,12 @@ hipError_t launch_cg_finish(const Box &b, double *x, const double *p, const CgSt
 }
 
 hipError_t launch_inner_start(const Box &b, const double *r64, CgState *outer, CgState *inner,
-                              double rtol2, int max_iter, float *rin, float *e, float *p,
+                              double rtol2, int max_iter, float *zin, float *e, float *p,
                               const float *minv32, double *part_a, double *part_b, hipStream_t s) {
   const int64_t L = b.L();
   const int64_t nt = vec_num_blocks(L);
   DISPATCH_N(b, inner_start_kernel, xcd_vec_grid(L), dim3(kVecThreads), 0, s, b, L, nt, r64, outer,
-             rin, e, p, minv32, part_a, part_b);
+             zin, e, p, minv32, part_a, part_b);
   hipError_t err = hipGetLastError();
   if (err != hipSuccess) return err;
   hipLaunchKernelGGL(inner_init_kernel, dim3(1), dim3(kFinThreads), 0, s, inner, part_a, part_b,
