@@ -604,6 +604,7 @@ __device__ inline void cg_beta_step(CgState *st, const double *__restrict__ part
 // it once all its loads are in flight and takes no further part if it returns
 // false (the solve has stopped; uniform over the launch).
 struct GivenScalars {
+  static constexpr bool kGiven = true;
   double alpha, beta;
   __device__ __forceinline__ bool operator()(double *a, double *b) const {
     *a = alpha;
@@ -619,6 +620,7 @@ struct GivenScalars {
 // work-group; sred: 32 doubles.
 template <int W>
 struct FoldBeta {
+  static constexpr bool kGiven = false;
   CgState *st;
   double *sred;
   PartialSums<W, 2> ps;
