@@ -90,7 +90,8 @@ typedef struct {
                                0: the faster one for the order and precision
                                   as measured on MI355X (matrix cores from
                                   N = 7 in FP64 and FP32 and from N = 9 in
-                                  BF16, vector ALUs below);
+                                  BF16, vector ALUs below; the inner CG
+                                  operator in BF16 from N = 8);
                                SEM_FLAG_MFMA: always the matrix-core kernel
                                   (D contractions as f64 MFMA, or f32 / bf16
                                   MFMA with FP32 accumulation);

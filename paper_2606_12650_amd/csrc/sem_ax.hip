@@ -102,7 +102,8 @@ template <class P>
 hipError_t ax_launch(const Box &b, int cls, int impl, const void *D, const void *G, void *u, void *w,
                      const void *z, void *x, CgState *cg, double *part,
                      hipStream_t s, bool stream_w, const CgFold &fold) {
-  const bool mfma = impl == kImplMfma || (impl == kImplDefault && op_uses_mfma(cls, b.N));
+  const bool mfma =
+      impl == kImplMfma || (impl == kImplDefault && (cg ? op_cg_mfma(cls, b.N) : op_uses_mfma(cls, b.N)));
   switch (b.N) {
 #define CASE(n)                                                                      \
   case n:                                                                            \

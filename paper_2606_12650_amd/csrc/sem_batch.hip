@@ -54,7 +54,7 @@ constexpr int kSchedThreads = 1024;
 
 // Operator tiles compiled for batches (order, elements per work-group).  An
 // order uses the vector-unit tiles or the matrix-core ones of its class, as
-// its single solves do (op_uses_mfma): the single-solve tile first, then a
+// its single solves do (op_cg_mfma): the single-solve tile first, then a
 // larger one where the FP64 LDS stays within 64 KiB and the work-group within
 // 512 (vector) or 1024 (matrix-core) threads.
 #define SEM_BATCH_TILES_VALU(X)                                               \
@@ -609,13 +609,13 @@ template <int N1, int EPB, bool MFMA>
 void fill_grid(BatchGrids &g, int cus) {
   constexpr int N = N1 - 1;
   constexpr int T = OpCfg<N1, EPB, MFMA>::THREADS;
-  if constexpr (op_uses_mfma(0, N) == MFMA)
+  if constexpr (op_cg_mfma(0, N) == MFMA)
     g.op[0][N][EPB] = resident_blocks(batch_op_kernel<N1, EPB, 0, MFMA>, T, cus, SEM_BATCH_GRID_MULT);
-  if constexpr (op_uses_mfma(1, N) == MFMA)
+  if constexpr (op_cg_mfma(1, N) == MFMA)
     g.op[1][N][EPB] = resident_blocks(batch_op_kernel<N1, EPB, 1, MFMA>, T, cus, SEM_BATCH_GRID_MULT);
-  if constexpr (op_uses_mfma(2, N) == MFMA)
+  if constexpr (op_cg_mfma(2, N) == MFMA)
     g.op[2][N][EPB] = resident_blocks(batch_op_kernel<N1, EPB, 2, MFMA>, T, cus, SEM_BATCH_GRID_MULT);
-  if constexpr (op_uses_mfma(3, N) == MFMA)
+  if constexpr (op_cg_mfma(3, N) == MFMA)
     g.op[3][N][EPB] = resident_blocks(batch_op_kernel<N1, EPB, 3, MFMA>, T, cus, SEM_BATCH_GRID_MULT);
 }
 
@@ -626,15 +626,15 @@ template <int N1, int EPB, bool MFMA>
 bool launch_op(int cls, const BatchGrids &g, int bound, const BatchSlot *slots, const BatchSched &sc, int bin,
                hipStream_t s) {
   constexpr int N = N1 - 1;
-  if (op_uses_mfma(cls, N) != MFMA) return false;
+  if (op_cg_mfma(cls, N) != MFMA) return false;
   const dim3 grid(bounded_grid(g.op[cls][N][EPB], bound)), threads(OpCfg<N1, EPB, MFMA>::THREADS);
-  if constexpr (op_uses_mfma(0, N) == MFMA)
+  if constexpr (op_cg_mfma(0, N) == MFMA)
     if (cls == 0) hipLaunchKernelGGL((batch_op_kernel<N1, EPB, 0, MFMA>), grid, threads, 0, s, slots, sc, bin);
-  if constexpr (op_uses_mfma(1, N) == MFMA)
+  if constexpr (op_cg_mfma(1, N) == MFMA)
     if (cls == 1) hipLaunchKernelGGL((batch_op_kernel<N1, EPB, 1, MFMA>), grid, threads, 0, s, slots, sc, bin);
-  if constexpr (op_uses_mfma(2, N) == MFMA)
+  if constexpr (op_cg_mfma(2, N) == MFMA)
     if (cls == 2) hipLaunchKernelGGL((batch_op_kernel<N1, EPB, 2, MFMA>), grid, threads, 0, s, slots, sc, bin);
-  if constexpr (op_uses_mfma(3, N) == MFMA)
+  if constexpr (op_cg_mfma(3, N) == MFMA)
     if (cls == 3) hipLaunchKernelGGL((batch_op_kernel<N1, EPB, 3, MFMA>), grid, threads, 0, s, slots, sc, bin);
   return true;
 }
@@ -731,7 +731,7 @@ struct BatchLaunch {
 
 int batch_default_epb(int cls, int N) {
   const int n1 = N + 1;
-  if (op_uses_mfma(cls, N)) {
+  if (op_cg_mfma(cls, N)) {
     const int nw = mfma_waves(n1);
     return nw >= 8 ? 1 : 8 / nw;
   }
@@ -740,7 +740,7 @@ int batch_default_epb(int cls, int N) {
 
 bool batch_epb_supported(int cls, int N, int epb) {
   if (cls < 0 || cls >= kBatchClasses) return false;
-  const bool mfma = op_uses_mfma(cls, N);
+  const bool mfma = op_cg_mfma(cls, N);
 #define SCASE_V(n_, epb_) \
   if (!mfma && N == n_ && epb == epb_) return true;
 #define SCASE_M(n_, epb_) \

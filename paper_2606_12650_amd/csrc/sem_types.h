@@ -251,6 +251,14 @@ enum GatherMode : int { kGatherAssembled = 0, kGatherMasked = 1, kGatherInverse 
 __host__ __device__ constexpr bool op_uses_mfma(int cls, int N) {
   return (cls == 0 || cls == 3 || cls == 1) ? N >= 7 : N >= 9;
 }
+// The same for the CG operator (x / p prologue).  It differs in BF16 at N = 8
+// only: 136 us on the vector tile (three LDS tiles, 162 threads), 89 us on the
+// matrix-core tile (24^3 box).  The bare operator is faster there too (102 ->
+// 73 us) but keeps the vector tile: its results, rounded to BF16 inside, would
+// no longer be those it has always given.
+__host__ __device__ constexpr bool op_cg_mfma(int cls, int N) {
+  return cls == 2 ? N >= 8 : op_uses_mfma(cls, N);
+}
 
 // Operator implementation request: the default above, or forced.
 enum OpImpl : int { kImplDefault = 0, kImplMfma = 1, kImplValu = 2 };
