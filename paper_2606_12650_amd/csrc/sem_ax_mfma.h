@@ -111,6 +111,20 @@ __device__ __forceinline__ int mfma_row(int g, int v) {
   return MfmaOps<P>::kF64 ? 4 * v + g : 4 * g + v;
 }
 
+// Whether the lanes find their LDS offsets once (MfmaLane: constant offsets in
+// the LDS instructions after that) or per access.  Once: BF16, whose operator
+// spent 87 % of its time issuing vector instructions (431 a wave at N = 9), and
+// FP32 at N = 8 and 9, where every access had missing rows to mask besides.
+// us, per access -> once: BF16 A.u N = 9 / 11, 7980 / 4096 elements 49 -> 42 /
+// 43 -> 38; FP32 N = 8 / 9, 8000 / 7980 elements 53 -> 45 / 58 -> 51.  FP64 is
+// not bound by issue (N = 9 65 -> 65, N = 8 80 -> 83), nor is FP32 at N = 7 and
+// from N = 10 (N = 11, 4096 elements 46 -> 47); BF16 at N = 12 loses a work-group
+// per CU to the three registers more (CG operator 155 -> 209).
+template <int N1, class P>
+constexpr bool mfma_fixed_offsets() {
+  return P::kBf16 ? N1 <= 12 : (!MfmaOps<P>::kF64 && (N1 == 9 || N1 == 10));
+}
+
 // LDS offset of the node with contracted/result index c and pair index q in
 // direction d (0: r, c = i; 1: s, c = j; 2: t, c = k).
 template <int N1>
@@ -123,10 +137,52 @@ __device__ __forceinline__ int mfma_point(int d, int c, int q) {
   return k * T::PLANE + j * T::P + i;
 }
 
+// Where a lane's column tile sits in the padded LDS tiles, for the three
+// directions (0: r, 1: s, 2: t).  Pair q = 16 tile + l % 16 of direction d has
+// its N1 values at base[d] + c stride(d).  Lanes past the last pair read the
+// last one and store nothing: a column of the product depends on its own
+// column of B alone.
+template <int N1, class P>
+struct MfmaLane {
+  using T = AxTile<N1>;
+  using M = MfmaTile<N1>;
+  static constexpr int GL = (N1 - 1) / 4;  // last group of four that holds a row
+  static constexpr int RL = N1 - 4 * GL;   // rows of that group (1..4)
+  int g;         // l / 16
+  bool qok;      // the lane has a pair
+  int rd[3];     // B operand: f32: c = g; bf16: c = 4 min(g, GL)
+  int rl[3];     // f32: c = min(g, RL - 1), for the last step
+  int st[3];     // result: m = 4 min(g, GL)
+  __host__ __device__ static constexpr int stride(int d) { return d == 0 ? 1 : (d == 1 ? T::P : T::PLANE); }
+  __device__ __forceinline__ MfmaLane(int tile, int l) {
+    if constexpr (!mfma_fixed_offsets<N1, P>()) return;
+    g = l >> 4;
+    const int q = tile * 16 + (l & 15);
+    qok = q < M::PL;
+    const int qc = qok ? q : M::PL - 1;
+    const int a = qc % N1, b = qc / N1;
+    const int base[3] = {b * T::PLANE + a * T::P, b * T::PLANE + a, b * T::P + a};
+    const int g4 = 4 * (g < GL ? g : GL);
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+      rd[d] = base[d] + (P::kBf16 ? g4 : g) * stride(d);
+      rl[d] = base[d] + (g < RL ? g : RL - 1) * stride(d);
+      st[d] = base[d] + g4 * stride(d);
+    }
+  }
+};
+
 __device__ __forceinline__ short mfma_bf16_bits(float v) {
   return (short)(__float_as_uint(v) >> 16);  // exact: v is a bfloat16 value
 }
 
+// D in LDS for the A operand: N1 x N1, or with the fixed offsets 16 x 16,
+// zero-padded, in rows of kDPitch values.
+constexpr int kDPitch = 17;
+template <int N1, class P>
+constexpr int mfma_d_size() {
+  return mfma_fixed_offsets<N1, P>() ? 16 * kDPitch : N1 * N1;
+}
 // The A operand of one lane: D (transpose = false) or D^T, zero-padded.
 template <int N1, class P>
 struct MfmaA {
@@ -139,23 +195,29 @@ struct MfmaA {
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         const int c = 4 * g + q;
-        const float v = (m < N1 && c < N1) ? (transpose ? sD[c * N1 + m] : sD[m * N1 + c]) : 0.0f;
-        ab[q] = mfma_bf16_bits(v);
+        if constexpr (mfma_fixed_offsets<N1, P>())
+          ab[q] = mfma_bf16_bits(transpose ? sD[c * kDPitch + m] : sD[m * kDPitch + c]);
+        else
+          ab[q] = mfma_bf16_bits((m < N1 && c < N1) ? (transpose ? sD[c * N1 + m] : sD[m * N1 + c]) : 0.0f);
       }
     } else {
 #pragma unroll
       for (int s = 0; s < MfmaTile<N1>::KS; ++s) {
         const int c = 4 * s + g;
-        a[s] = (m < N1 && c < N1) ? (transpose ? sD[c * N1 + m] : sD[m * N1 + c]) : (TC)0;
+        if constexpr (mfma_fixed_offsets<N1, P>())
+          a[s] = transpose ? sD[c * kDPitch + m] : sD[m * kDPitch + c];
+        else
+          a[s] = (m < N1 && c < N1) ? (transpose ? sD[c * N1 + m] : sD[m * N1 + c]) : (TC)0;
       }
     }
   }
 };
 
-// Column tile `tile` of direction d: the four result rows of this lane for
+// Without the fixed offsets: column tile `tile` of direction d, the four result
+// rows of this lane for
 // pair q = 16 tile + l % 16, from the LDS tile `in`.
 template <int N1, class P>
-__device__ __forceinline__ typename MfmaOps<P>::Acc mfma_contract(const MfmaA<N1, P> &A,
+__device__ __forceinline__ typename MfmaOps<P>::Acc mfma_contract_at(const MfmaA<N1, P> &A,
                                                                  const typename P::TC *in, int d,
                                                                  int tile, int l) {
   using M = MfmaTile<N1>;
@@ -196,7 +258,7 @@ __device__ __forceinline__ typename MfmaOps<P>::Acc mfma_contract(const MfmaA<N1
 
 // Store the lane's result rows of a column tile to `out` (rows < N1 only).
 template <int N1, class P>
-__device__ __forceinline__ void mfma_store(typename P::TC *out, const typename MfmaOps<P>::Acc &acc,
+__device__ __forceinline__ void mfma_store_at(typename P::TC *out, const typename MfmaOps<P>::Acc &acc,
                                            int d, int tile, int l) {
   const int g = l >> 4;
   const int q = tile * 16 + (l & 15);
@@ -208,8 +270,52 @@ __device__ __forceinline__ void mfma_store(typename P::TC *out, const typename M
   }
 }
 
+// Direction D of the lane's column tile: its four result rows, from the LDS
+// tile `in`.  Rows past the last index are zeros (D is too, but a value there
+// may not be finite).
+template <int D, int N1, class P>
+__device__ __forceinline__ mfma_v4f mfma_contract(const MfmaA<N1, P> &A, const MfmaLane<N1, P> &L, const float *in) {
+  using M = MfmaTile<N1>;
+  using Ln = MfmaLane<N1, P>;
+  constexpr int ST = Ln::stride(D);
+  mfma_v4f acc = {0, 0, 0, 0};
+  const float *p = in + L.rd[D];
+  if constexpr (P::kBf16) {
+    mfma_v4s b;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      // the last group's missing rows read its last one
+      const float v = u < Ln::RL ? p[u * ST] : p[L.g < Ln::GL ? u * ST : (Ln::RL - 1) * ST];
+      b[u] = mfma_bf16_bits(4 * L.g + u < N1 ? v : 0.0f);
+    }
+    return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(A.ab, b, acc, 0, 0, 0);
+  } else {
+    float b[M::KS];
+#pragma unroll
+    for (int s = 0; s < M::KS - 1; ++s) b[s] = p[4 * s * ST];
+    const float v = in[L.rl[D] + 4 * (M::KS - 1) * ST];
+    b[M::KS - 1] = (Ln::RL == 4 || L.g < Ln::RL) ? v : 0.0f;
+#pragma unroll
+    for (int s = 0; s < M::KS; ++s) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(A.a[s], b[s], acc, 0, 0, 0);
+    return acc;
+  }
+}
+
+// Store the lane's result rows 4 g + v of its column tile to `out` (rows < N1
+// only).
+template <int D, int N1, class P>
+__device__ __forceinline__ void mfma_store(float *out, const MfmaLane<N1, P> &L, const mfma_v4f &acc) {
+  using Ln = MfmaLane<N1, P>;
+  constexpr int ST = Ln::stride(D);
+  if (!L.qok) return;
+  float *p = out + L.st[D];
+#pragma unroll
+  for (int v = 0; v < 4; ++v)
+    if (v < Ln::RL ? L.g <= Ln::GL : L.g < Ln::GL) p[v * ST] = acc[v];
+}
+
 // Same contract as ax_tile<N1, EPB, P, CG, OPQ> with blockDim = MfmaCfg<N1>::THREADS
-// (EPB = MfmaCfg<N1>::EPB).  LDS: sD N1*N1 TC, s1/s2/s3 EPB * AxTile<N1>::TILE
+// (EPB = MfmaCfg<N1>::EPB).  LDS: sD mfma_d_size TC, s1/s2/s3 EPB * AxTile<N1>::TILE
 // TC each, sred blockDim / 64 doubles.  SW (without CG): w is written with
 // non-temporal stores.
 //
@@ -251,7 +357,14 @@ __device__ __forceinline__ void ax_tile_mfma(int64_t E, int64_t e0, const typena
   TC *R = s2 + slot * T::TILE;
   TC *S = s3 + slot * T::TILE;
 
-  for (int t = tid; t < N1 * N1; t += blockDim.x) sD[t] = Dg[t];
+  if constexpr (mfma_fixed_offsets<N1, P>()) {
+    for (int t = tid; t < 256; t += blockDim.x) {
+      const int dm = t >> 4, dc = t & 15;
+      sD[dm * kDPitch + dc] = (dm < N1 && dc < N1) ? Dg[dm * N1 + dc] : (TC)0;
+    }
+  } else {
+    for (int t = tid; t < N1 * N1; t += blockDim.x) sD[t] = Dg[t];
+  }
 
   // prologue in the flat layout.  Every load is issued unconditionally (lanes
   // without a node read entry 0 and drop the value) so that all are in flight
@@ -314,18 +427,33 @@ __device__ __forceinline__ void ax_tile_mfma(int64_t E, int64_t e0, const typena
   __syncthreads();
 
   // gradient: r and s to LDS, t kept until the operand tile is free
+  constexpr bool FIXED = mfma_fixed_offsets<N1, P>();
+  const MfmaLane<N1, P> L(tile, l);  // (fixed offsets only)
   MfmaA<N1, P> A;
   A.load(sD, false, l);
   Acc ut = {0, 0, 0, 0};
   if (mine && tiled) {
-    const Acc ur = mfma_contract<N1, P>(A, U, 0, tile, l);
-    const Acc us = mfma_contract<N1, P>(A, U, 1, tile, l);
-    ut = mfma_contract<N1, P>(A, U, 2, tile, l);
-    mfma_store<N1, P>(R, ur, 0, tile, l);
-    mfma_store<N1, P>(S, us, 1, tile, l);
+    if constexpr (FIXED) {
+      const Acc ur = mfma_contract<0>(A, L, U);
+      const Acc us = mfma_contract<1>(A, L, U);
+      ut = mfma_contract<2>(A, L, U);
+      mfma_store<0>(R, L, ur);
+      mfma_store<1>(S, L, us);
+    } else {
+      const Acc ur = mfma_contract_at<N1, P>(A, U, 0, tile, l);
+      const Acc us = mfma_contract_at<N1, P>(A, U, 1, tile, l);
+      ut = mfma_contract_at<N1, P>(A, U, 2, tile, l);
+      mfma_store_at<N1, P>(R, ur, 0, tile, l);
+      mfma_store_at<N1, P>(S, us, 1, tile, l);
+    }
   }
   __syncthreads();  // every wave has read the operand tile
-  if (mine && tiled) mfma_store<N1, P>(U, ut, 2, tile, l);
+  if (mine && tiled) {
+    if constexpr (FIXED)
+      mfma_store<2>(U, L, ut);
+    else
+      mfma_store_at<N1, P>(U, ut, 2, tile, l);
+  }
   if constexpr (LATE_G) load_gk();
   __syncthreads();
 
@@ -349,12 +477,21 @@ __device__ __forceinline__ void ax_tile_mfma(int64_t E, int64_t e0, const typena
   // tile's pairs in R (r), S (s) and U (t)
   A.load(sD, true, l);
   if (mine && tiled) {
-    const Acc vr = mfma_contract<N1, P>(A, R, 0, tile, l);
-    const Acc vs = mfma_contract<N1, P>(A, S, 1, tile, l);
-    const Acc vt = mfma_contract<N1, P>(A, U, 2, tile, l);
-    mfma_store<N1, P>(R, vr, 0, tile, l);
-    mfma_store<N1, P>(S, vs, 1, tile, l);
-    mfma_store<N1, P>(U, vt, 2, tile, l);
+    if constexpr (FIXED) {
+      const Acc vr = mfma_contract<0>(A, L, R);
+      const Acc vs = mfma_contract<1>(A, L, S);
+      const Acc vt = mfma_contract<2>(A, L, U);
+      mfma_store<0>(R, L, vr);
+      mfma_store<1>(S, L, vs);
+      mfma_store<2>(U, L, vt);
+    } else {
+      const Acc vr = mfma_contract_at<N1, P>(A, R, 0, tile, l);
+      const Acc vs = mfma_contract_at<N1, P>(A, S, 1, tile, l);
+      const Acc vt = mfma_contract_at<N1, P>(A, U, 2, tile, l);
+      mfma_store_at<N1, P>(R, vr, 0, tile, l);
+      mfma_store_at<N1, P>(S, vs, 1, tile, l);
+      mfma_store_at<N1, P>(U, vt, 2, tile, l);
+    }
   }
   __syncthreads();
 

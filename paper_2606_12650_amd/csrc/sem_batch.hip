@@ -259,10 +259,10 @@ __global__ void __launch_bounds__((OpCfg<N1, EPB, MFMA>::THREADS))
   using TC = typename P::TC;
   using T = AxTile<N1>;
   using C = OpCfg<N1, EPB, MFMA>;
-  static_assert((int)sizeof(TC) * (N1 * N1 + C::kTiles * EPB * T::TILE) + 8 * C::SRED <= 64 * 1024,
+  static_assert((int)sizeof(TC) * ((MFMA ? mfma_d_size<N1, P>() : N1 * N1) + C::kTiles * EPB * T::TILE) + 8 * C::SRED <= 64 * 1024,
                 "batched operator tile exceeds 64 KiB of LDS");
   static_assert(C::THREADS <= (MFMA ? 1024 : 512), "batched operator tile exceeds its work-group");
-  __shared__ TC sD[N1 * N1];
+  __shared__ TC sD[MFMA ? mfma_d_size<N1, P>() : N1 * N1];
   __shared__ TC s1[EPB * T::TILE];
   __shared__ TC s2[EPB * T::TILE];
   __shared__ TC s3[C::kTiles == 3 ? EPB * T::TILE : 1];

@@ -96,7 +96,7 @@ __device__ __forceinline__ void ax_mfma_body(int64_t E, const typename P::TC *__
                                              double *__restrict__ part) {
   using C = MfmaCfg<N1>;
   using TC = typename P::TC;
-  __shared__ TC sD[N1 * N1];
+  __shared__ TC sD[mfma_d_size<N1, P>()];
   __shared__ TC s1[C::EPB * AxTile<N1>::TILE];
   __shared__ TC s2[C::EPB * AxTile<N1>::TILE];
   __shared__ TC s3[C::EPB * AxTile<N1>::TILE];
