@@ -341,10 +341,10 @@ __device__ inline int64_t xcd_tile(int64_t ntiles) {
   return (b % kNumXcd) * per + b / kNumXcd;
 }
 
-// The tile of this work-group in a launch of tile_grid(ntiles) (a value past
-// the last tile: none).
-__device__ inline int64_t chunk_tile(int64_t ntiles) {
-  if (!tiles_chunked(ntiles)) return xcd_tile(ntiles);
+// The tile of this work-group in a launch of tile_grid(ntiles, chunked) (a
+// value past the last tile: none).
+__device__ inline int64_t chunk_tile(int64_t ntiles, bool chunked) {
+  if (!chunked) return xcd_tile(ntiles);
   const int64_t x = blockIdx.x % kNumXcd, j = blockIdx.x / kNumXcd;
   const int64_t t = (j / kTileChunk * kNumXcd + x) * kTileChunk + j % kTileChunk;
   return t < ntiles ? ntiles - 1 - t : t;

@@ -157,7 +157,7 @@ __global__ void __launch_bounds__(MfmaCfg<N1>::THREADS, (mfma_waves_per_simd<N1,
 // units and LDS; every array index is a constant (unrolled), so that the
 // columns stay in registers.  A plane of coordinates is read by its own plane's
 // contractions only, so plane k of the three diagonal factors replaces it once
-// every thread is past it (one barrier per plane, no further LDS tile).
+// every thread is past it (no further LDS tile).
 template <int N1>
 __global__ void __launch_bounds__(AxCfg<N1>::THREADS)
     setup_geom_kernel(Box b, double amp, const double *__restrict__ Dg,
@@ -220,7 +220,10 @@ __global__ void __launch_bounds__(AxCfg<N1>::THREADS)
   const double wij = nodes[N1 + i] * nodes[N1 + j];
   const int64_t base = e * NP + ij;
   double cross[N1];            // the diagonal's part from the mixed factors
-  double g0 = 0, g1 = 0, g2 = 0;  // diagonal factors of the plane before
+  // the diagonal factors: up to N = 5 in registers until every plane is done
+  // (one barrier in all), else to LDS plane by plane
+  constexpr bool HELD = N1 <= 6;
+  double gd[3][HELD ? N1 : 1];
 #pragma unroll
   for (int k = 0; k < N1; ++k) {
     double J[3][3];
@@ -275,24 +278,28 @@ __global__ void __launch_bounds__(AxCfg<N1>::THREADS)
     }
     const double Dkk = Dg[k * N1 + k];
     cross[k] = 2.0 * Dii * Djj * g[1] + 2.0 * Dii * Dkk * g[2] + 2.0 * Djj * Dkk * g[4];
-    if (k > 0) {  // every thread is past plane k - 1 (the barrier below)
-      const int o = (k - 1) * T::PLANE + j * T::P + i;
-      SX[o] = g0;
-      SY[o] = g1;
-      SZ[o] = g2;
+    gd[0][HELD ? k : 0] = g[0];
+    gd[1][HELD ? k : 0] = g[3];
+    gd[2][HELD ? k : 0] = g[5];
+    if constexpr (!HELD) {
+      __syncthreads();  // every thread is past plane k
+      const int o = k * T::PLANE + j * T::P + i;
+      SX[o] = g[0];
+      SY[o] = g[3];
+      SZ[o] = g[5];
     }
-    g0 = g[0];
-    g1 = g[3];
-    g2 = g[5];
-    __syncthreads();
-  }
-  {
-    const int o = (N1 - 1) * T::PLANE + j * T::P + i;
-    SX[o] = g0;
-    SY[o] = g1;
-    SZ[o] = g2;
   }
   __syncthreads();
+  if constexpr (HELD) {
+#pragma unroll
+    for (int k = 0; k < N1; ++k) {
+      const int o = k * T::PLANE + j * T::P + i;
+      SX[o] = gd[0][k];
+      SY[o] = gd[1][k];
+      SZ[o] = gd[2][k];
+    }
+    __syncthreads();
+  }
 #pragma unroll
   for (int l = 0; l < N1; ++l) {
     const double a = sD[l * N1 + i], bb = sD[l * N1 + j];
@@ -323,8 +330,8 @@ __global__ void __launch_bounds__(AxCfg<N1>::THREADS)
 template <int N1, int MODE, typename T>
 __global__ void __launch_bounds__(kVecThreads)
     gather_kernel(Box b, int64_t L, int64_t ntiles, const T *__restrict__ wl, T *__restrict__ out,
-                  float *__restrict__ out32) {
-  const int64_t tile = chunk_tile(ntiles);
+                  float *__restrict__ out32, int chunked) {
+  const int64_t tile = chunk_tile(ntiles, chunked != 0);
   if (tile >= ntiles) return;
   const LinItems<N1> P(b, tile, (int)threadIdx.x);
   T res[kVecItems];
@@ -369,10 +376,10 @@ __global__ void __launch_bounds__(kVecThreads)
 template <int N1, int MODE, typename T, int V>
 __global__ void __launch_bounds__((UpdTile<N1, T, V>::BLOCK))
     gather_col_kernel(Box b, int64_t ntiles, const T *__restrict__ wl, T *__restrict__ out,
-                      float *__restrict__ out32) {
+                      float *__restrict__ out32, int chunked) {
   using U = UpdTile<N1, T, V>;
   __shared__ double sA[U::LDS];
-  const int64_t tile = chunk_tile(ntiles);
+  const int64_t tile = chunk_tile(ntiles, chunked != 0);
   if (tile >= ntiles) return;
   const ColumnPos<N1, T, V> p(b, tile, (int)threadIdx.x);
   double S[U::KN];
@@ -419,7 +426,7 @@ __global__ void __launch_bounds__((UpdTile<N1, TV, V>::BLOCK))
   __shared__ double sA[UpdTile<N1, TV, V>::LDS];
   if (st->done) return;
   const GivenScalars sc{st->alpha, 0.0};
-  const int64_t tile = chunk_tile(ntiles);
+  const int64_t tile = chunk_tile(ntiles, tiles_chunked(ntiles));
   TileSums t{0.0, 0.0};
   if (tile < ntiles)
     t = cg_update_tile<N1, TV, V>(b, tile, r, w, minv, sc, sA, sred, (int)threadIdx.x);
@@ -440,7 +447,7 @@ __global__ void __launch_bounds__((UpdTile<N1, TV>::BLOCK))
   __shared__ double sA[UpdTile<N1, TV>::LDS];
   if (st->done) return;
   const GivenScalars sc{st->alpha, 0.0};
-  const int64_t tile = chunk_tile(ntiles);
+  const int64_t tile = chunk_tile(ntiles, tiles_chunked(ntiles));
   if (tile >= ntiles) return;
   const TileSums t = cg_update_tile<N1, TV, 0, true>(b, tile, r, w, minv, sc, sA, sred, (int)threadIdx.x);
   if (threadIdx.x == 0) {
@@ -461,7 +468,7 @@ __global__ void __launch_bounds__((UpdTile<N1, TV>::BLOCK))
   __shared__ double sred[2 * W];
   __shared__ double sfold[kFinGroup / 64];  // not sred: no barrier follows its last read
   __shared__ double sA[UpdTile<N1, TV>::LDS];
-  const int64_t tile = chunk_tile(ntiles);
+  const int64_t tile = chunk_tile(ntiles, tiles_chunked(ntiles));
   if (tile >= ntiles) return;
   const FoldAlpha<W> sc(st, part_pap, n_op, sfold);
   const TileSums t = cg_update_tile<N1, TV>(b, tile, r, w, minv, sc, sA, sred, (int)threadIdx.x);

@@ -124,12 +124,21 @@ inline int64_t vec_grid_blocks(int64_t n) { return 8 * ((vec_num_blocks(n) + 7) 
 // XCD has its share).  Measured on MI355X, 32^3 box, one contiguous range per
 // XCD forwards -> chunks backwards, us: FP64 update N = 7 101 -> 96, N = 11
 // 407 -> 369 (and the operator after it 1012 -> 993); FP32 N = 11 197 -> 191.
+// A gather, whose vectors an operator application has just written whole, takes
+// the chunks only where they are too large to stay in the cache together
+// (gather_chunked): N = 7, 134 MB, masked A.u 241 -> 228 us; N = 3 / 4 / 6, 57
+// to 74 MB, the gather alone 23 -> 27 / 25 -> 27 / 27 -> 30 us in chunks.  The
+// Jacobi set-up's gather follows the writing of all of G and takes them at any
+// size (N = 3 / 4 / 6 48 -> 33 / 53 -> 39 / 56 -> 43 us).
 constexpr int kTileChunk = 32;
 constexpr int64_t kChunkTiles = 4096;
 __host__ __device__ constexpr bool tiles_chunked(int64_t ntiles) { return ntiles >= kChunkTiles; }
-inline int64_t tile_grid(int64_t ntiles) {
-  const int64_t m = tiles_chunked(ntiles) ? 8 * kTileChunk : 8;
+inline int64_t tile_grid(int64_t ntiles, bool chunked) {
+  const int64_t m = chunked ? 8 * kTileChunk : 8;
   return m * ((ntiles + m - 1) / m);
+}
+inline bool gather_chunked(int64_t ntiles, int64_t vector_bytes, bool inverse) {
+  return tiles_chunked(ntiles) && (inverse || vector_bytes >= (int64_t)128 << 20);
 }
 
 // Tiles of the CG update (the gather-scatter pulled into z -= alpha Minv w) are
@@ -216,7 +225,10 @@ inline int64_t upd_num_tiles(const Box &b, bool f64, int v = 0) {
   return (b.E() + sh.ept - 1) / sh.ept * sh.kp;
 }
 // Launch size of the update.
-inline int64_t upd_grid_blocks(const Box &b, bool f64, int v = 0) { return tile_grid(upd_num_tiles(b, f64, v)); }
+inline int64_t upd_grid_blocks(const Box &b, bool f64, int v = 0) {
+  const int64_t nt = upd_num_tiles(b, f64, v);
+  return tile_grid(nt, tiles_chunked(nt));
+}
 
 // Whether the update writes r with non-temporal stores: vectors larger than
 // the last-level cache.  There a plain store displaces the part of w the
