@@ -336,8 +336,10 @@ int sem_export(sem_ctx *ctx, int field, double *dst_dev, void *stream);
  * the scalars.  After every tenth iteration of a step, and after its last, the
  * solves that have stopped go through the phases they owe (the last update of
  * x; outer correction, true residual and inner restart of a mixed solve) and
- * the lists are rebuilt.  Every solve's arithmetic and reduction order are
- * those of sem_cg, so an FP64 solve gives the same bits in a batch as alone.
+ * the lists are rebuilt; in a step of one iteration they go through the phase
+ * they are in beside the iteration of the others.  Every solve's arithmetic and
+ * reduction order are those of sem_cg, so an FP64 solve gives the same bits in
+ * a batch as alone.
  * Solves join and leave between steps (continuous batching); the step's
  * graph is captured again only when the set of bins in use, the tiles or the
  * launch sizes (powers of two of the work the occupied slots can have) change.

@@ -786,6 +786,7 @@ struct sem_batch {
   std::vector<sem_ctx *> ctx;          // null for a free slot
   std::vector<semk::BatchStatus> status;
   semk::BatchTiles tiles;
+  bool joined;  // a mixed solve joined since the last step: its inner start is due
   hipGraphExec_t graph;
   // what the captured graph was built for: stream, iterations, the operator
   // bins it launches and the tiles
@@ -898,6 +899,7 @@ int sem_batch_create(int max_slots, void *dev_ws, size_t ws_bytes, void *stream,
   std::memset(&B->tiles, 0, sizeof(B->tiles));
   for (int c = 0; c < semk::kBatchClasses; ++c)
     for (int n = 1; n <= semk::kBatchOrders; ++n) B->tiles.epb[c][n] = semk::batch_default_epb(c, n);
+  B->joined = false;
   B->graph = nullptr;
   B->graph_stream = nullptr;
   B->graph_iters = 0;
@@ -1018,6 +1020,7 @@ int sem_batch_add(sem_batch *B, sem_ctx *ctx, const double *b, double *x, const 
   B->slots[q] = S;
   B->ctx[q] = ctx;
   ctx->in_batch = 1;
+  if (S.phase == semk::kPhaseRestart) B->joined = true;
   *slot_out = q;
   return SEM_OK;
 }
@@ -1056,6 +1059,10 @@ int sem_batch_step(sem_batch *B, int iters, void *stream) {
     } else {
       (void)hipGetLastError();
     }
+  }
+  if (B->joined) {  // ahead of the captured step, so that joins do not change it
+    SEM_HIP(semk::launch_batch_join(B->d_slots, B->max_slots, B->sched, B->tiles, bins, bounds, B->d_status, s));
+    B->joined = false;
   }
   if (s != nullptr && B->graph && B->graph_stream == s && B->graph_iters == iters &&
       B->graph_bins == bins) {

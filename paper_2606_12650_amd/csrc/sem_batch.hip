@@ -22,7 +22,8 @@
 // empty lists, 95 of 200 us; now a stopped solve waits for five iterations on
 // average, four to nine times in a solve of several hundred.  24 solves of
 // 64..1024 elements in FP32: 253 -> 134 ms; 64 of 64..4096: 589 -> 434 ms (FP64
-// 671 -> 625).
+// 671 -> 625).  A step of one iteration, which would pay for all of that each
+// time, runs every phase beside its iteration instead (single()).
 //
 // Every item is computed by the same device functions as a single solve
 // (sem_ax_tile.h, sem_cg_dev.h) and each solve's reductions are summed in
@@ -505,8 +506,10 @@ __global__ void __launch_bounds__(kFinThreads)
     cg_alpha_step(S.st_in, S.part_el, S.E, sred);
 }
 
+// outer: the true residuals of this step's outer steps are in (single()), and
+// are finished here as well.
 __global__ void __launch_bounds__(kFinThreads)
-    batch_beta_kernel(BatchSlot *__restrict__ slots) {
+    batch_beta_kernel(BatchSlot *__restrict__ slots, int outer) {
   __shared__ double sred[2 * (kFinThreads / 64)];
   BatchSlot &S = slots[blockIdx.x];
   if (!S.active) return;
@@ -526,6 +529,9 @@ __global__ void __launch_bounds__(kFinThreads)
         S.phase = kPhaseInnerDone;
       }
     }
+  } else if (phase == kPhaseOuterOp && outer) {
+    outer_finish_step(S.st, S.part_rr, S.vtiles, sred);
+    if (threadIdx.x == 0) S.phase = S.st->done != kRunning ? kPhaseFinished : kPhaseRestart;
   }
 }
 
@@ -681,8 +687,9 @@ struct BatchLaunch {
   void schedule() const {
     hipLaunchKernelGGL(batch_schedule_kernel, dim3(1), dim3(kSchedThreads), 0, s, slots, sched, tiles);
   }
-  bool iteration() const {
-    if (!operators(0, 2)) return false;
+  // One iteration; outer: the outer steps' operators and true residuals too.
+  bool iteration(bool outer) const {
+    if (!operators(0, outer ? 3 : 2)) return false;
     hipLaunchKernelGGL(batch_alpha_kernel, dim3(max_slots), dim3(kFinThreads), 0, s, slots);
 #define UCASE(n_)                                                                                        \
   if (in_use(0, n_))                                                                                     \
@@ -695,7 +702,9 @@ struct BatchLaunch {
                        dim3(BatchUpd<n_ + 1, true>::BLOCK), 0, s, slots, sched, batch_upd_list(1, n_));
     SEM_BATCH_ORDERS(UCASE)
 #undef UCASE
-    hipLaunchKernelGGL(batch_beta_kernel, dim3(max_slots), dim3(kFinThreads), 0, s, slots);
+    if (outer)
+      hipLaunchKernelGGL(batch_resid_kernel, dim3(g.resid), dim3(kVecThreads), 0, s, slots, sched);
+    hipLaunchKernelGGL(batch_beta_kernel, dim3(max_slots), dim3(kFinThreads), 0, s, slots, outer ? 1 : 0);
     return true;
   }
 
@@ -712,7 +721,7 @@ struct BatchLaunch {
 
   // Every solve that has stopped goes through the phases it owes: an FP64
   // solve its last x += alpha p; a mixed one the outer correction, the true
-  // residual and the restart of its inner solve.  Then the lists are rebuilt.
+  // residual and the restart of its inner solve.
   bool phases() const {
     finish(f64(), mixed());
     if (mixed()) {
@@ -722,7 +731,20 @@ struct BatchLaunch {
       hipLaunchKernelGGL(batch_outer_kernel, dim3(max_slots), dim3(kFinThreads), 0, s, slots);
       finish(false, true);
     }
+    return true;
+  }
+
+  // A step of one iteration: a solve is in one phase, and its phase's work runs
+  // beside the iteration of the others, so an outer step takes two such steps.
+  // Launches of a mixed batch of five orders: 22, against 27 with the
+  // iteration first and every phase after it (from two iterations on it is the
+  // other way round: 44 against 39).  us a step on MI355X, every phase after the
+  // iteration and an inner start in front -> this: one FP32 solve of 512
+  // elements at N = 7 59 -> 36, fifteen of five orders 120 -> 94.
+  bool single() const {
     schedule();
+    if (!iteration(mixed())) return false;
+    finish(f64(), mixed());
     return true;
   }
 };
@@ -793,14 +815,25 @@ hipError_t launch_batch_step(BatchSlot *slots, int max_slots, const BatchSched &
   const BatchGrids *g = current_grids();
   if (!g) return hipErrorNotInitialized;
   const BatchLaunch B{slots, max_slots, sched, tiles, bins, bounds, status, *g, s};
-  // solves that joined since the last step: a mixed one starts its inner solve
-  if (B.mixed()) B.finish(false, true);
-  B.schedule();
+  if (iters == 1) {
+    if (!B.single()) return hipErrorInvalidValue;
+    return hipGetLastError();
+  }
   for (int it = 0; it < iters; ++it) {
-    if (!B.iteration()) return hipErrorInvalidValue;
+    if (it % kBatchPhaseEvery == 0) B.schedule();
+    if (!B.iteration(false)) return hipErrorInvalidValue;
     if ((it + 1) % kBatchPhaseEvery == 0 || it + 1 == iters)
       if (!B.phases()) return hipErrorInvalidValue;
   }
+  return hipGetLastError();
+}
+
+hipError_t launch_batch_join(BatchSlot *slots, int max_slots, const BatchSched &sched, const BatchTiles &tiles,
+                             uint64_t bins, const BatchBounds &bounds, BatchStatus *status, hipStream_t s) {
+  const BatchGrids *g = current_grids();
+  if (!g) return hipErrorNotInitialized;
+  const BatchLaunch B{slots, max_slots, sched, tiles, bins, bounds, status, *g, s};
+  B.finish(false, true);
   return hipGetLastError();
 }
 

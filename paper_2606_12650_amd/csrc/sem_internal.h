@@ -24,12 +24,15 @@ hipError_t batch_prepare();
 // operator launch per bin of classes 0..2 set in `bins` (bit cls * 11 + N - 1),
 // the alpha steps, one update launch per order and family in use and the beta
 // steps; the phases advance after every kBatchPhaseEvery of them and after the
-// last (bits kBatchBins and kBatchBins + 1 of `bins`: FP64 and mixed solves
-// present).
+// last, or beside the iteration if there is only one (bits kBatchBins and
+// kBatchBins + 1 of `bins`: FP64 and mixed solves present).
 constexpr int kBatchPhaseEvery = 10;
 hipError_t launch_batch_step(BatchSlot *slots, int max_slots, const BatchSched &sched, const BatchTiles &tiles,
                              uint64_t bins, const BatchBounds &bounds, BatchStatus *status, int iters,
                              hipStream_t s);
+// The inner start of the mixed solves that joined since the last step.
+hipError_t launch_batch_join(BatchSlot *slots, int max_slots, const BatchSched &sched, const BatchTiles &tiles,
+                             uint64_t bins, const BatchBounds &bounds, BatchStatus *status, hipStream_t s);
 
 // ---------------------------------------------------------------- launchers
 // All return the hipError_t of the launch (hipGetLastError after it).
