@@ -437,7 +437,7 @@ hipError_t rtc_gather(const Box &b, const double *wl, double *out, int mode, hip
   Box bb = b;
   int64_t L = b.L(), nt = vec_num_blocks(L);
   float *out32 = nullptr;
-  const bool ch = gather_chunked(nt, L * (int64_t)sizeof(double), mode == kGatherInverse);
+  const bool ch = gather_chunked(nt, L * (int64_t)sizeof(double), true, mode == kGatherInverse);
   int chunked = ch ? 1 : 0;
   void *args[] = {&bb, &L, &nt, &wl, &out, &out32, &chunked};
   return launch(b.N, k, dim3((unsigned)tile_grid(nt, ch)), dim3(kVecThreads), s, args);

@@ -123,13 +123,19 @@ inline int64_t vec_grid_blocks(int64_t n) { return 8 * ((vec_num_blocks(n) + 7) 
 // range per XCD (about one launch wave: the order does not matter, and every
 // XCD has its share).  Measured on MI355X, 32^3 box, one contiguous range per
 // XCD forwards -> chunks backwards, us: FP64 update N = 7 101 -> 96, N = 11
-// 407 -> 369 (and the operator after it 1012 -> 993); FP32 N = 11 197 -> 191.
+// 407 -> 369 (and the operator after it 1012 -> 993); a whole FP64 iteration at
+// N = 3 / 7 / 11 with vectors of 458 MB 1521 -> 1469 / 1302 -> 1258 / 1300 ->
+// 1263.  In FP32 an iteration gains 3 % or nothing (N = 11, 227 MB: 686 -> 683).
 // A gather, whose vectors an operator application has just written whole, takes
 // the chunks only where they are too large to stay in the cache together
-// (gather_chunked): N = 7, 134 MB, masked A.u 241 -> 228 us; N = 3 / 4 / 6, 57
-// to 74 MB, the gather alone 23 -> 27 / 25 -> 27 / 27 -> 30 us in chunks.  The
-// Jacobi set-up's gather follows the writing of all of G and takes them at any
-// size (N = 3 / 4 / 6 48 -> 33 / 53 -> 39 / 56 -> 43 us).
+// (gather_chunked).  us per masked A.u, one range per XCD -> chunks: FP64 N = 4
+// / 7 / 11 at 61 to 97 MB 128 -> 130 / 105 -> 103 / 117 -> 117, at 126 to 128 MB
+// 270 -> 266 / 215 -> 209 / 233 -> 237, at 150 MB 324 -> 324 / 253 -> 252 / 288 ->
+// 286, at 250 MB 637 -> 591 / 499 -> 464 / 522 -> 491; FP32 N = 4 / 7 / 11 at 135
+// MB 359 -> 369 / 253 -> 261 / 307 -> 310, at 150 MB 400 -> 411 / 285 -> 293 / 344
+// -> 344, at 180 MB 506 -> 488 / 374 -> 363 / 420 -> 415.  The Jacobi set-up's
+// gather follows the writing of all of G and takes them at any size (N = 3 / 4 /
+// 6 48 -> 33 / 53 -> 39 / 56 -> 43 us).
 constexpr int kTileChunk = 32;
 constexpr int64_t kChunkTiles = 4096;
 __host__ __device__ constexpr bool tiles_chunked(int64_t ntiles) { return ntiles >= kChunkTiles; }
@@ -137,8 +143,8 @@ inline int64_t tile_grid(int64_t ntiles, bool chunked) {
   const int64_t m = chunked ? 8 * kTileChunk : 8;
   return m * ((ntiles + m - 1) / m);
 }
-inline bool gather_chunked(int64_t ntiles, int64_t vector_bytes, bool inverse) {
-  return tiles_chunked(ntiles) && (inverse || vector_bytes >= (int64_t)128 << 20);
+inline bool gather_chunked(int64_t ntiles, int64_t vector_bytes, bool f64, bool inverse) {
+  return tiles_chunked(ntiles) && (inverse || vector_bytes >= (int64_t)(f64 ? 128 : 160) << 20);
 }
 
 // Tiles of the CG update (the gather-scatter pulled into z -= alpha Minv w) are

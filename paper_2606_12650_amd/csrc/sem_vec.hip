@@ -291,12 +291,12 @@ void gather_launch(const Box &b, const T *wl, T *out, float *out32, hipStream_t 
   constexpr int V = MODE == kGatherInverse ? 0 : kGatherShape;
   if constexpr (UpdTile<N1, T, V>::LINEAR) {
     const int64_t L = b.L(), nt = vec_num_blocks(L);
-    const bool ch = gather_chunked(nt, L * (int64_t)sizeof(T), MODE == kGatherInverse);
+    const bool ch = gather_chunked(nt, L * (int64_t)sizeof(T), sizeof(T) == 8, MODE == kGatherInverse);
     hipLaunchKernelGGL((gather_kernel<N1, MODE, T>), dim3((unsigned)tile_grid(nt, ch)), dim3(kVecThreads), 0, s,
                        b, L, nt, wl, out, out32, (int)ch);
   } else {
     const int64_t nt = upd_num_tiles(b, sizeof(T) == 8, V);
-    const bool ch = gather_chunked(nt, b.L() * (int64_t)sizeof(T), MODE == kGatherInverse);
+    const bool ch = gather_chunked(nt, b.L() * (int64_t)sizeof(T), sizeof(T) == 8, MODE == kGatherInverse);
     hipLaunchKernelGGL((gather_col_kernel<N1, MODE, T, V>), dim3((unsigned)tile_grid(nt, ch)),
                        dim3(UpdTile<N1, T, V>::BLOCK), 0, s, b, nt, wl, out, out32, (int)ch);
   }
