@@ -1024,7 +1024,7 @@ def main(argv=None) -> int:
         "cg_event_ms_per_step": ev_ms / args.steps,
         # the unfused (19 + 2s)-word floor per point and iteration over the
         # time, against the peak: a throughput on a fixed byte count, not the
-        # bytes this design moves (17 words; see cg_hbm_traffic_frac)
+        # bytes this design moves (16 words; see cg_hbm_traffic_frac)
         "cg_unfused_floor_bytes_frac": cg_bytes_per_iter * timed_iters / wall / 1e9 / HBM_PEAK_GBS,
         "cg_hbm_traffic_frac": _cg_traffic_frac(timed_iters, wall),
         "ax_local_us": ax_s * 1e6,

@@ -267,7 +267,7 @@ int sem_gs(int32_t n_rows, const int32_t *offsets_dev, const int32_t *ids_dev, i
  *                         matrix-core tile, 2 the vector-ALU tile (as
  *                         sem_mesh_desc.flags, per precision family);
  *   SEM_KNOB_UPDATE_TILE  the shape of the CG update tile (the gather-scatter
- *                         fused into r -= alpha A p): threads per (i, j)
+ *                         fused into z -= alpha Minv A p): threads per (i, j)
  *                         column, elements per tile, plane ranges.
  * `prec` names the family: SEM_F64 for the FP64 operator and update (sem_ax,
  * the FP64 CG and the outer steps of the mixed one), SEM_F32 or SEM_BF16 for

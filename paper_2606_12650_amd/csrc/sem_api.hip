@@ -203,7 +203,8 @@ struct sem_ctx {
   Layout lay;
   char *ws;
   size_t ws_bytes;
-  double *D, *nodes, *G, *minv, *r, *p, *w, *part_ax, *part_rr, *part_rz;
+  double *D, *nodes, *G, *minv, *r, *p, *w, *part_ax, *part_rr, *part_rz;  // r: z = Minv r in FP64 CG, the true
+                                                                           // residual in mixed solves
   CgState *st;
   // low-precision copy (null when desc.lowprec == SEM_F64)
   float *Dlo, *minv32, *e, *zin, *pin, *win;

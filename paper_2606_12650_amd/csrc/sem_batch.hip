@@ -10,9 +10,9 @@
 // and registers of the single-solve kernel of that order), so a list of small
 // elements is not held to the resources of the largest order.  Each work-group
 // takes a contiguous range of its list's items and finds their solves by
-// searching the prefix sums; a launch takes no more work-groups than the
-// batch's own solves can use (BatchBounds: the full persistent grid of an
-// almost empty list cost 5-10 us a launch).
+// searching the prefix sums; an operator or update launch takes no more
+// work-groups than the batch's own solves can use (BatchBounds: the full
+// persistent grid of an almost empty list cost 5-10 us a launch).
 //
 // The lists hold for up to kBatchPhaseEvery iterations: a solve that stops in
 // between is skipped by the kernels that walk them.  Only then do the phases
@@ -216,8 +216,8 @@ __global__ void __launch_bounds__(kSchedThreads)
   }
 }
 
-// The two finishing lists, rebuilt when the phases advance: FP64 solves that stopped (x owes alpha p) and mixed
-// solves whose inner solve ended or whose inner solve restarts.
+// The two finishing lists, rebuilt when the phases advance: FP64 solves that
+// stopped (x owes alpha p) and mixed solves whose inner solve ended or restarts.
 __global__ void __launch_bounds__(128)
     batch_fin_schedule_kernel(const BatchSlot *__restrict__ slots, BatchSched sc) {
   const int wave = threadIdx.x >> 6;
@@ -411,7 +411,7 @@ __global__ void __launch_bounds__((BatchUpd<N1, MIXED>::BLOCK))
   // the slot's operands and state, loaded once per slot (not once per item)
   int cur = -1, active = 0, ut = 0;
   Box box;
-  TV *r = nullptr;
+  TV *z = nullptr;
   const TV *wv = nullptr, *minv = nullptr;
   double alpha = 0.0;
   double *prr = nullptr, *prz = nullptr;
@@ -434,9 +434,9 @@ __global__ void __launch_bounds__((BatchUpd<N1, MIXED>::BLOCK))
       prr = S.part_rr;
       prz = S.part_rz;
       if constexpr (MIXED) {
-        r = S.zin; wv = S.win; minv = S.minv32;
+        z = S.zin; wv = S.win; minv = S.minv32;
       } else {
-        r = S.r; wv = S.w; minv = S.minv;
+        z = S.r; wv = S.w; minv = S.minv;
       }
     }
     if (!active) {  // the slot has no update in this iteration: skip its items
@@ -445,7 +445,7 @@ __global__ void __launch_bounds__((BatchUpd<N1, MIXED>::BLOCK))
     }
     const int tile = w - first;
     if (tile >= ut) continue;
-    const TileSums t = cg_update_tile<N1, TV>(box, tile, r, wv, minv, GivenScalars{alpha, 0.0}, sA, sred,
+    const TileSums t = cg_update_tile<N1, TV>(box, tile, z, wv, minv, GivenScalars{alpha, 0.0}, sA, sred,
                                               (int)threadIdx.x);
     if (threadIdx.x == 0) {
       prr[tile] = t.a;

@@ -27,7 +27,7 @@ struct TileSums {
 // alone (p = z + beta p), and the update, which loads Minv anyway for z -=
 // alpha Minv o (mask o QQ^T w), has r back as z / Minv for the two reductions.
 // An iteration then reads Minv once: 16 words per point instead of 17 (FP64
-// operator at N = 7 on the 32^3 box 258 -> 238 us, at N = 11 978 -> 903).
+// operator at N = 7 on the 32^3 box 259 -> 233 us, at N = 11 951 -> 888).
 // Masked nodes (Minv = 0) carry z = 0 and take no part in the update.  Without
 // a preconditioner z = r, and beta p is rounded before it is added, so the
 // plain CG's bits are those of a loop on r.
@@ -65,7 +65,7 @@ __device__ inline TileSums cg_init_tile(const Box &b, int64_t L, int64_t tile,
 // sums ||r||_c^2 and <r, z>_c with r = z / Minv (FP64 even for FP32 vectors).
 //
 // The tile is element-aligned (UpdTile): each thread owns KN planes of one
-// (i, j) column of an element, so every load of w, r and Minv is a
+// (i, j) column of an element, so every load of w, z and Minv is a
 // coalesced run of a plane, and the copies of a node that sit in other
 // elements are reached in pairs along one direction at a time:
 //   P = w(node) + w(y copy)                  pair across a y face,
@@ -149,7 +149,7 @@ __device__ __forceinline__ void upd_column_sum(const ColumnW<KN, TV> &c, int kb,
 }
 
 // Linear tile: the items of a thread are taken kLinGroup at a time, all
-// loads of a group (r, Minv and every present copy of w) before any sum, so
+// loads of a group (z, Minv and every present copy of w) before any sum, so
 // a group costs one HBM round trip.
 constexpr int kLinGroup = 4;
 

@@ -395,11 +395,9 @@ __device__ inline Node<N1> node_at(const Box &b, int64_t idx) {
 // copies of the node in w, added in ascending element-local index order.
 // Along each direction a node has one copy, or two when it sits on a face
 // shared with the neighbouring element; the second copy is a fixed address
-// step away (next element, local index N -> 0).  A missing copy adds +0.0,
-// which leaves the sum unchanged.  load_copies issues all eight candidate
-// loads unconditionally (a missing copy reads the node itself), so no branch
-// separates them.  Every copy of a node computes the same sum in the same
-// order: the result is exactly continuous.
+// step away (next element, local index N -> 0).  A missing copy is not loaded
+// and adds +0.0, which leaves the sum unchanged.  Every copy of a node computes
+// the same sum in the same order: the result is exactly continuous.
 template <int N1>
 struct Copies {
   int64_t addr[8];
@@ -427,23 +425,6 @@ __device__ inline Copies<N1> copies_of(const Box &b, const Node<N1> &n, int64_t 
   return c;
 }
 
-template <int N1, typename T>
-__device__ inline void load_copies(const T *__restrict__ w, const Copies<N1> &c, T (&v)[8]) {
-#pragma unroll
-  for (int q = 0; q < 8; ++q) v[q] = w[c.addr[q]];
-}
-
-template <int N1, typename T>
-__device__ inline double sum_copies(const Copies<N1> &c, const T (&v)[8]) {
-  double s = 0.0;
-#pragma unroll
-  for (int q = 0; q < 8; ++q) s += c.valid[q] ? (double)v[q] : 0.0;
-  return s;
-}
-
-// The same sum with the loads of missing copies masked off (fewer memory
-// requests for interior nodes; the form the FP64 kernels measured fastest
-// with).
 template <int N1, typename T>
 __device__ inline double gather_copies(const T *__restrict__ w, const Box &b, const Node<N1> &n,
                                        int64_t idx) {

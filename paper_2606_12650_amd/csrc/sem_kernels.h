@@ -403,13 +403,13 @@ __global__ void __launch_bounds__((UpdTile<N1, T, V>::BLOCK))
 template <int N1>
 __global__ void __launch_bounds__(kVecThreads)
     cg_init_kernel(Box b, int64_t L, int64_t ntiles, const double *__restrict__ bvec,
-                   double *__restrict__ x, double *__restrict__ r, double *__restrict__ p,
+                   double *__restrict__ x, double *__restrict__ z, double *__restrict__ p,
                    const double *__restrict__ minv, double *__restrict__ part_rz,
                    double *__restrict__ part_bb) {
   __shared__ double sred[2 * (kVecThreads / 64)];
   const int64_t tile = xcd_tile(ntiles);
   TileSums t{0.0, 0.0};
-  if (tile < ntiles) t = cg_init_tile<N1>(b, L, tile, bvec, x, r, p, minv, sred);
+  if (tile < ntiles) t = cg_init_tile<N1>(b, L, tile, bvec, x, z, p, minv, sred);
   if (threadIdx.x == 0) {
     part_rz[tile] = t.a;
     part_bb[tile] = t.b;
@@ -419,7 +419,7 @@ __global__ void __launch_bounds__(kVecThreads)
 // V: the update tile shape (upd_shape), one kernel per candidate.
 template <int N1, typename TV, int V = 0>
 __global__ void __launch_bounds__((UpdTile<N1, TV, V>::BLOCK))
-    cg_update_kernel(Box b, int64_t ntiles, TV *__restrict__ r, const TV *__restrict__ w,
+    cg_update_kernel(Box b, int64_t ntiles, TV *__restrict__ z, const TV *__restrict__ w,
                      const TV *__restrict__ minv, CgState *__restrict__ st,
                      double *__restrict__ part_rr, double *__restrict__ part_rz) {
   __shared__ double sred[2 * (UpdTile<N1, TV, V>::BLOCK / 64)];
@@ -429,18 +429,18 @@ __global__ void __launch_bounds__((UpdTile<N1, TV, V>::BLOCK))
   const int64_t tile = chunk_tile(ntiles, tiles_chunked(ntiles));
   TileSums t{0.0, 0.0};
   if (tile < ntiles)
-    t = cg_update_tile<N1, TV, V>(b, tile, r, w, minv, sc, sA, sred, (int)threadIdx.x);
+    t = cg_update_tile<N1, TV, V>(b, tile, z, w, minv, sc, sA, sred, (int)threadIdx.x);
   if (threadIdx.x == 0) {
     part_rr[tile] = t.a;
     part_rz[tile] = t.b;
   }
 }
 
-// The update on the default tile with r written by non-temporal stores
+// The update on the default tile with z written by non-temporal stores
 // (upd_streams_z), for vectors larger than the last-level cache.
 template <int N1, typename TV>
 __global__ void __launch_bounds__((UpdTile<N1, TV>::BLOCK))
-    cg_update_stream_kernel(Box b, int64_t ntiles, TV *__restrict__ r, const TV *__restrict__ w,
+    cg_update_stream_kernel(Box b, int64_t ntiles, TV *__restrict__ z, const TV *__restrict__ w,
                             const TV *__restrict__ minv, CgState *__restrict__ st,
                             double *__restrict__ part_rr, double *__restrict__ part_rz) {
   __shared__ double sred[2 * (UpdTile<N1, TV>::BLOCK / 64)];
@@ -449,7 +449,7 @@ __global__ void __launch_bounds__((UpdTile<N1, TV>::BLOCK))
   const GivenScalars sc{st->alpha, 0.0};
   const int64_t tile = chunk_tile(ntiles, tiles_chunked(ntiles));
   if (tile >= ntiles) return;
-  const TileSums t = cg_update_tile<N1, TV, 0, true>(b, tile, r, w, minv, sc, sA, sred, (int)threadIdx.x);
+  const TileSums t = cg_update_tile<N1, TV, 0, true>(b, tile, z, w, minv, sc, sA, sred, (int)threadIdx.x);
   if (threadIdx.x == 0) {
     part_rr[tile] = t.a;
     part_rz[tile] = t.b;
@@ -460,7 +460,7 @@ __global__ void __launch_bounds__((UpdTile<N1, TV>::BLOCK))
 // alpha step from the operator's n_op partials part_pap inside.
 template <int N1, typename TV>
 __global__ void __launch_bounds__((UpdTile<N1, TV>::BLOCK))
-    cg_update_fold_kernel(Box b, int64_t ntiles, TV *__restrict__ r, const TV *__restrict__ w,
+    cg_update_fold_kernel(Box b, int64_t ntiles, TV *__restrict__ z, const TV *__restrict__ w,
                           const TV *__restrict__ minv, CgState *__restrict__ st,
                           double *__restrict__ part_rr, double *__restrict__ part_rz,
                           const double *__restrict__ part_pap, int n_op) {
@@ -471,7 +471,7 @@ __global__ void __launch_bounds__((UpdTile<N1, TV>::BLOCK))
   const int64_t tile = chunk_tile(ntiles, tiles_chunked(ntiles));
   if (tile >= ntiles) return;
   const FoldAlpha<W> sc(st, part_pap, n_op, sfold);
-  const TileSums t = cg_update_tile<N1, TV>(b, tile, r, w, minv, sc, sA, sred, (int)threadIdx.x);
+  const TileSums t = cg_update_tile<N1, TV>(b, tile, z, w, minv, sc, sA, sred, (int)threadIdx.x);
   if (threadIdx.x == 0) {
     part_rr[tile] = t.a;
     part_rz[tile] = t.b;

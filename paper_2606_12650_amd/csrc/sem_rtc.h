@@ -38,9 +38,9 @@ hipError_t rtc_ax_f64(const Box &b, const double *D, const double *G, double *u,
                       const double *z, double *x, CgState *cg, double *part,
                       hipStream_t s);
 hipError_t rtc_gather(const Box &b, const double *wl, double *out, int mode, hipStream_t s);
-hipError_t rtc_cg_init(const Box &b, const double *bvec, double *x, double *r, double *p,
+hipError_t rtc_cg_init(const Box &b, const double *bvec, double *x, double *z, double *p,
                        const double *minv, double *part_a, double *part_b, hipStream_t s);
-hipError_t rtc_cg_update(const Box &b, double *r, const double *w, const double *minv, CgState *st,
+hipError_t rtc_cg_update(const Box &b, double *z, const double *w, const double *minv, CgState *st,
                          double *part_rr, double *part_rz, hipStream_t s);
 hipError_t rtc_fill_c(const Box &b, double *c, hipStream_t s);
 

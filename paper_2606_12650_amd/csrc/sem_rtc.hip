@@ -443,20 +443,20 @@ hipError_t rtc_gather(const Box &b, const double *wl, double *out, int mode, hip
   return launch(b.N, k, dim3((unsigned)tile_grid(nt, ch)), dim3(kVecThreads), s, args);
 }
 
-hipError_t rtc_cg_init(const Box &b, const double *bvec, double *x, double *r, double *p,
+hipError_t rtc_cg_init(const Box &b, const double *bvec, double *x, double *z, double *p,
                        const double *minv, double *part_a, double *part_b, hipStream_t s) {
   Box bb = b;
   int64_t L = b.L(), nt = vec_num_blocks(L);
-  void *args[] = {&bb, &L, &nt, &bvec, &x, &r, &p, &minv, &part_a, &part_b};
+  void *args[] = {&bb, &L, &nt, &bvec, &x, &z, &p, &minv, &part_a, &part_b};
   return launch(b.N, kRtcCgInit, dim3((unsigned)vec_grid_blocks(L)), dim3(kVecThreads), s, args);
 }
 
-hipError_t rtc_cg_update(const Box &b, double *r, const double *w, const double *minv, CgState *st,
+hipError_t rtc_cg_update(const Box &b, double *z, const double *w, const double *minv, CgState *st,
                          double *part_rr, double *part_rz, hipStream_t s) {
   const Shape sh = shape(b.N);
   Box bb = b;
   int64_t nt = upd_num_tiles(b, true);
-  void *args[] = {&bb, &nt, &r, &w, &minv, &st, &part_rr, &part_rz};
+  void *args[] = {&bb, &nt, &z, &w, &minv, &st, &part_rr, &part_rz};
   return launch(b.N, kRtcCgUpdate, dim3((unsigned)upd_grid_blocks(b, true)), dim3(sh.upd_block), s,
                 args);
 }

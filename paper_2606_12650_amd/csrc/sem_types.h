@@ -118,7 +118,7 @@ inline int64_t vec_grid_blocks(int64_t n) { return 8 * ((vec_num_blocks(n) + 7) 
 // walk the mesh backwards, in chunks of kTileChunk consecutive tiles per XCD
 // (sem_device.h, chunk_tile): the operator walks it forwards, so what it wrote
 // last, and the 256 MB last-level cache still holds, is read first, and the
-// other way round for r at the next operator launch; a chunk keeps the x
+// other way round for z at the next operator launch; a chunk keeps the x
 // copies, and most y copies, in one XCD's L2.  Fewer tiles keep one contiguous
 // range per XCD (about one launch wave: the order does not matter, and every
 // XCD has its share).  Measured on MI355X, 32^3 box, one contiguous range per
@@ -177,7 +177,7 @@ constexpr int kUpdVariants = 4;
 
 // The shape of the sem_ax gathers (assembled and masked), beside the update's
 // candidates.  Up to order 8 the update's default; above, where the gather has
-// neither r nor the diagonal to load, more elements per tile (the x copies
+// neither z nor the diagonal to load, more elements per tile (the x copies
 // inside it come from LDS) and plane ranges beat the linear tile.  us per
 // masked gather on MI355X, linear -> this: FP64 N = 9, 5083 elements 20.4 ->
 // 17.3; N = 10, 4096 21.0 -> 18.1; N = 11, 21952 92 -> 83; N = 12, 1000 11.1 ->
@@ -236,7 +236,7 @@ inline int64_t upd_grid_blocks(const Box &b, bool f64, int v = 0) {
   return tile_grid(nt, tiles_chunked(nt));
 }
 
-// Whether the update writes r with non-temporal stores: vectors larger than
+// Whether the update writes z with non-temporal stores: vectors larger than
 // the last-level cache.  There a plain store displaces the part of w the
 // update has yet to read (FP64 N = 11, 453 MB a vector: 369 -> 350 us); a
 // vector that fits is wanted there by the next operator launch (N = 7, 134 MB:
@@ -307,6 +307,7 @@ struct BatchSlot {
   double eta2;
   int64_t E, L;
   const double *D, *G, *b;
+  // r: z = Minv r in an FP64 solve, the true residual in a mixed one
   double *minv, *r, *p, *w, *x;
   const float *Dlo;
   const void *Glo;
@@ -328,11 +329,11 @@ struct BatchStatus {
 // is the FP64 CG iterations of FP64 solves, classes 1 and 2 the FP32 and BF16
 // inner iterations of mixed solves, class 3 the FP64 true-residual operator
 // of their outer steps.  Lists kBatchFinList and kBatchFinList + 1 hold the
-// streaming tiles of the FP64 and mixed solves whose phase ends this
-// iteration (rebuilt after the beta launch), kBatchResidList those of the
-// mixed solves computing an outer true residual; after them come the update
-// tiles of the CG update, per order, of the FP64 solves (family 0, the slots
-// of bin (0, N)) and of the inner solves (family 1, bins (1, N) and (2, N)).
+// streaming tiles of the FP64 and mixed solves with finishing work (a stopped
+// FP64 solve; an outer correction or an inner start), rebuilt by each finishing
+// pass; kBatchResidList those of the mixed solves computing an outer true
+// residual; after them come the update tiles of the CG update, per order, of the
+// FP64 solves (family 0, the slots of bin (0, N)) and of the inner solves (family 1, bins (1, N) and (2, N)).
 constexpr int kBatchOrders = 11;  // batches take orders 1..11
 constexpr int kBatchClasses = 4;
 constexpr int kBatchBins = kBatchClasses * kBatchOrders;
@@ -346,10 +347,12 @@ __host__ __device__ inline int batch_upd_list(int fam, int N) {
   return kBatchUpdLists + fam * kBatchOrders + (N - 1);
 }
 
-// Work lists that the schedule kernel rebuilds on the device at the start of
-// every batched iteration (kBatchLists lists, max_slots entries each): the
-// slots with work in the bin in ascending order, the exclusive prefix sums of
-// their item counts (one more entry: the total), and [count, total].
+// Work lists that the schedule kernel builds on the device (kBatchLists lists,
+// max_slots entries each) at the start of a step, after every kBatchPhaseEvery
+// of its iterations and before the outer operators of a phase change.  Solves
+// may stop while a list holds: the kernels that walk it skip them.  A list is:
+// the slots with work in the bin in ascending order, the exclusive prefix sums
+// of their item counts (one more entry: the total), and [count, total].
 struct BatchSched {
   int *meta;
   int *slot;
@@ -362,9 +365,10 @@ struct BatchTiles {
   int epb[kBatchClasses][kBatchOrders + 1];
 };
 
-// Upper bounds of the work in a batch's lists, from its occupied slots: the
-// items of each operator bin and of each update list.  A launch takes no more
-// work-groups than its bound.  Rounded up to powers of two, so that a captured
+// Upper bounds of the work in a batch's operator and update lists, from its
+// occupied slots.  Those launches take no more work-groups than their bound; the
+// finishing and residual launches, which only the phase changes make, keep their
+// full persistent grids.  Rounded up to powers of two, so that a captured
 // step outlives most joins and leaves.
 struct BatchBounds {
   int op[kBatchBins];

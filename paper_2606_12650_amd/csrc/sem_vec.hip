@@ -198,7 +198,7 @@ inline dim3 vec_grid(int64_t n) { return dim3((unsigned)vec_num_blocks(n)); }
 
 // The update of order N1 - 1 with tile shape V (upd_shape).
 template <int N1, typename TV, int V>
-hipError_t update_launch(const Box &b, TV *r, const TV *w, const TV *minv, CgState *st,
+hipError_t update_launch(const Box &b, TV *z, const TV *w, const TV *minv, CgState *st,
                          double *part_rr, double *part_rz, hipStream_t s, const CgFold &fold) {
   constexpr bool f64 = sizeof(TV) == 8;
   if constexpr (!upd_variant_exists(N1, f64, V)) {
@@ -207,17 +207,17 @@ hipError_t update_launch(const Box &b, TV *r, const TV *w, const TV *minv, CgSta
     if (fold.n_op > 0) {
       if constexpr (V == 0)
         hipLaunchKernelGGL((cg_update_fold_kernel<N1, TV>), dim3((unsigned)upd_grid_blocks(b, f64)),
-                           dim3(UpdTile<N1, TV>::BLOCK), 0, s, b, upd_num_tiles(b, f64), r, w, minv, st,
+                           dim3(UpdTile<N1, TV>::BLOCK), 0, s, b, upd_num_tiles(b, f64), z, w, minv, st,
                            part_rr, part_rz, fold.part_pap, fold.n_op);
       else
         return hipErrorInvalidValue;
     } else if (V == 0 && upd_streams_z(b, f64)) {
       hipLaunchKernelGGL((cg_update_stream_kernel<N1, TV>), dim3((unsigned)upd_grid_blocks(b, f64)),
-                         dim3(UpdTile<N1, TV>::BLOCK), 0, s, b, upd_num_tiles(b, f64), r, w, minv, st, part_rr,
+                         dim3(UpdTile<N1, TV>::BLOCK), 0, s, b, upd_num_tiles(b, f64), z, w, minv, st, part_rr,
                          part_rz);
     } else {
       hipLaunchKernelGGL((cg_update_kernel<N1, TV, V>), dim3((unsigned)upd_grid_blocks(b, f64, V)),
-                         dim3(UpdTile<N1, TV, V>::BLOCK), 0, s, b, upd_num_tiles(b, f64, V), r, w,
+                         dim3(UpdTile<N1, TV, V>::BLOCK), 0, s, b, upd_num_tiles(b, f64, V), z, w,
                          minv, st, part_rr, part_rz);
     }
     return hipGetLastError();
@@ -225,17 +225,17 @@ hipError_t update_launch(const Box &b, TV *r, const TV *w, const TV *minv, CgSta
 }
 
 template <typename TV>
-hipError_t update_typed(const Box &b, int variant, TV *r, const TV *w, const TV *minv, CgState *st,
+hipError_t update_typed(const Box &b, int variant, TV *z, const TV *w, const TV *minv, CgState *st,
                         double *part_rr, double *part_rz, hipStream_t s, const CgFold &fold) {
   if (b.E() == 0) return hipSuccess;
   switch (b.N) {
 #define UCASE(n_)                                                                                \
   case n_:                                                                                       \
     switch (variant) {                                                                           \
-      case 0: return update_launch<n_ + 1, TV, 0>(b, r, w, minv, st, part_rr, part_rz, s, fold); \
-      case 1: return update_launch<n_ + 1, TV, 1>(b, r, w, minv, st, part_rr, part_rz, s, fold); \
-      case 2: return update_launch<n_ + 1, TV, 2>(b, r, w, minv, st, part_rr, part_rz, s, fold); \
-      case 3: return update_launch<n_ + 1, TV, 3>(b, r, w, minv, st, part_rr, part_rz, s, fold); \
+      case 0: return update_launch<n_ + 1, TV, 0>(b, z, w, minv, st, part_rr, part_rz, s, fold); \
+      case 1: return update_launch<n_ + 1, TV, 1>(b, z, w, minv, st, part_rr, part_rz, s, fold); \
+      case 2: return update_launch<n_ + 1, TV, 2>(b, z, w, minv, st, part_rr, part_rz, s, fold); \
+      case 3: return update_launch<n_ + 1, TV, 3>(b, z, w, minv, st, part_rr, part_rz, s, fold); \
       default: return hipErrorInvalidValue;                                                      \
     }
     UCASE(1) UCASE(2) UCASE(3) UCASE(4) UCASE(5) UCASE(6)
@@ -332,16 +332,16 @@ hipError_t launch_gather_f32(const Box &b, const float *wl, float *out, int mode
   return gather_typed<float>(b, wl, out, mode, nullptr, s);
 }
 
-hipError_t launch_cg_init(const Box &b, const double *bvec, double *x, double *r, double *p,
+hipError_t launch_cg_init(const Box &b, const double *bvec, double *x, double *z, double *p,
                           const double *minv, CgState *st, double *part_a, double *part_b,
                           hipStream_t s) {
   const int64_t L = b.L();
   const int64_t nt = vec_num_blocks(L);
   hipError_t e;
   if (rtc_order(b.N)) {
-    e = rtc_cg_init(b, bvec, x, r, p, minv, part_a, part_b, s);
+    e = rtc_cg_init(b, bvec, x, z, p, minv, part_a, part_b, s);
   } else {
-    DISPATCH_N(b, cg_init_kernel, xcd_vec_grid(L), dim3(kVecThreads), 0, s, b, L, nt, bvec, x, r, p,
+    DISPATCH_N(b, cg_init_kernel, xcd_vec_grid(L), dim3(kVecThreads), 0, s, b, L, nt, bvec, x, z, p,
                minv, part_a, part_b);
     e = hipGetLastError();
   }
@@ -368,20 +368,20 @@ hipError_t launch_cg_beta_pending(CgState *st, const double *part_rr, const doub
   return hipGetLastError();
 }
 
-hipError_t launch_cg_update(const Box &b, int variant, double *r, const double *w, const double *minv,
+hipError_t launch_cg_update(const Box &b, int variant, double *z, const double *w, const double *minv,
                             CgState *st, double *part_rr, double *part_rz, hipStream_t s,
                             const CgFold &fold) {
   if (rtc_order(b.N)) {
     if (variant != 0) return hipErrorInvalidValue;
-    return b.E() == 0 ? hipSuccess : rtc_cg_update(b, r, w, minv, st, part_rr, part_rz, s);
+    return b.E() == 0 ? hipSuccess : rtc_cg_update(b, z, w, minv, st, part_rr, part_rz, s);
   }
-  return update_typed<double>(b, variant, r, w, minv, st, part_rr, part_rz, s, fold);
+  return update_typed<double>(b, variant, z, w, minv, st, part_rr, part_rz, s, fold);
 }
 
-hipError_t launch_cg_update_f32(const Box &b, int variant, float *r, const float *w, const float *minv,
+hipError_t launch_cg_update_f32(const Box &b, int variant, float *z, const float *w, const float *minv,
                                 CgState *st, double *part_rr, double *part_rz, hipStream_t s,
                                 const CgFold &fold) {
-  return update_typed<float>(b, variant, r, w, minv, st, part_rr, part_rz, s, fold);
+  return update_typed<float>(b, variant, z, w, minv, st, part_rr, part_rz, s, fold);
 }
 
 hipError_t launch_cg_finish(const Box &b, double *x, const double *p, const CgState *st,
