@@ -158,6 +158,14 @@ __global__ void __launch_bounds__(MfmaCfg<N1>::THREADS, (mfma_waves_per_simd<N1,
 // columns stay in registers.  A plane of coordinates is read by its own plane's
 // contractions only, so plane k of the three diagonal factors replaces it once
 // every thread is past it (no further LDS tile).
+//
+// From N = 13 on, the orders compiled at run time, the loops over the planes
+// stay rolled, or run two planes at a time where their number is even (the
+// diagonal's mixed part then waits in its place in memory): unrolled they made
+// the first set-up of such an order wait for the compiler, N = 13 / 14 / 15 1.10
+// / 1.23 / 1.15 s against 0.57 / 0.56 / 0.53 s, and gained nothing (17^3 boxes
+// 605 / 692 / 791 us unrolled, 488 / 690 / 739 so; N = 15 one plane at a time
+// 815).
 template <int N1>
 __global__ void __launch_bounds__(AxCfg<N1>::THREADS)
     setup_geom_kernel(Box b, double amp, const double *__restrict__ Dg,
@@ -219,12 +227,14 @@ __global__ void __launch_bounds__(AxCfg<N1>::THREADS)
 
   const double wij = nodes[N1 + i] * nodes[N1 + j];
   const int64_t base = e * NP + ij;
-  double cross[N1];            // the diagonal's part from the mixed factors
+  constexpr bool ROLLED = N1 > 13;
+  constexpr int UNROLL = !ROLLED ? N1 : (N1 % 2 == 0 ? 2 : 1);  // of the loops over the planes
+  double cross[ROLLED ? 1 : N1];           // the diagonal's part from the mixed factors
   // the diagonal factors: up to N = 5 in registers until every plane is done
   // (one barrier in all), else to LDS plane by plane
   constexpr bool HELD = N1 <= 6;
   double gd[3][HELD ? N1 : 1];
-#pragma unroll
+#pragma unroll UNROLL
   for (int k = 0; k < N1; ++k) {
     double J[3][3];
 #pragma unroll
@@ -277,7 +287,11 @@ __global__ void __launch_bounds__(AxCfg<N1>::THREADS)
       }
     }
     const double Dkk = Dg[k * N1 + k];
-    cross[k] = 2.0 * Dii * Djj * g[1] + 2.0 * Dii * Dkk * g[2] + 2.0 * Djj * Dkk * g[4];
+    const double mixed = 2.0 * Dii * Djj * g[1] + 2.0 * Dii * Dkk * g[2] + 2.0 * Djj * Dkk * g[4];
+    if constexpr (!ROLLED)
+      cross[k] = mixed;
+    else if (active)
+      diag[base + k * PL] = mixed;
     gd[0][HELD ? k : 0] = g[0];
     gd[1][HELD ? k : 0] = g[3];
     gd[2][HELD ? k : 0] = g[5];
@@ -306,7 +320,7 @@ __global__ void __launch_bounds__(AxCfg<N1>::THREADS)
     Da[l] = a * a;
     Db[l] = bb * bb;
   }
-#pragma unroll
+#pragma unroll UNROLL
   for (int k = 0; k < N1; ++k) {
     double d = 0.0;
 #pragma unroll
@@ -316,8 +330,12 @@ __global__ void __launch_bounds__(AxCfg<N1>::THREADS)
       d += Db[l] * SY[k * T::PLANE + l * T::P + i];
       d += c * c * SZ[l * T::PLANE + j * T::P + i];
     }
-    d += cross[k];
-    if (active) diag[base + k * PL] = d;
+    if constexpr (ROLLED) {
+      if (active) diag[base + k * PL] += d;
+    } else {
+      d += cross[k];
+      if (active) diag[base + k * PL] = d;
+    }
   }
 }
 
